@@ -629,16 +629,6 @@ dcem_status dcem_scene_upload(dcem_ctx* c, const dcem_scene_desc* s) {
   c->no = s->n_objects;
   c->pad = (float)(4e-6 * (2.0 * R + 1.0));
   c->h_face_object = FO;
-  {
-    // faces per group (the static geometry, each moving object): the sort
-    // keys of the build hold a face's rank within its group
-    std::vector<int32_t> per((size_t)c->no + 1, 0);
-    for (int32_t o : FO) ++per[(size_t)(o + 1)];
-    int32_t most = 1;
-    for (int32_t v : per) most = std::max(most, v);
-    c->face_bits = 0;
-    while ((int64_t(1) << c->face_bits) < most) ++c->face_bits;
-  }
   HIP_TRY(upload(c->ref_vertices, V, c->stream), "upload vertices");
   HIP_TRY(upload(c->vertices, V, c->stream), "upload vertices");
   HIP_TRY(upload(c->tris, T, c->stream), "upload tris");

@@ -196,11 +196,10 @@ struct dcem_ctx {
   dcem::DevBuf tree_info;                            // uint32 [0]: 4-wide nodes, [1]: root leaf-slot mask,
                                                      // [2]: cross nodes, [3], [4]: refit list length and block ticket
   dcem::DevBuf tri4;                                 // leaf triangles in slot order (Leaf [n4][4])
-  dcem::DevBuf face_build;                           // build scratch: face boxes, keys, order and ranks
-  int face_bits = 0;                                 // bits of a face's rank among its group's faces
+  dcem::DevBuf face_build;                           // build scratch: face codes, boxes, keys and order
   // the last full build's keys (in `morton`): grouped by object, and their layout
   bool keys_grouped = false;
-  int key_words_built = 1, key_rank_bits = 0, key_face_bits = 0;
+  int key_words_built = 1, key_rank_bits = 0, key_low_bits = 0;   // (key_low_bits: below the group prefix)
   double subtree_ratio = 1.0;                        // SAH of the last build relative to the last full build
 
   // -- rays and cache
