@@ -339,9 +339,8 @@ def cpu_baseline(scene):
 
 # Algorithmic bytes of one closest-hit launch (what the traversal must read
 # and write, counted once per use; nothing assumed cached):
-#   per-thread kernel: 128 B per 4-wide node fetched from memory (the top
-#     three levels are read from LDS and not counted), 48 B per triangle test,
-#     per ray 13 B (direction, order entry, state), per segment 4 B (face log)
+#   packet kernel: 128 B per 4-wide node a packet or a ray by itself fetches,
+#     48 B per ray-triangle test, per ray 13 B (direction, order entry, state), per segment 4 B (face log)
 #     + 32 B when the segment cache is kept, 8 B per capture record;
 #   group kernel: per node visit its four 32-byte slots (a leaf slot reads its
 #     48-byte triangle instead: +16 B per triangle test), per ray 42 B (list
@@ -483,7 +482,7 @@ def main():
     out["ms_stages"] = {k: float(np.mean([s[k] for s in stats])) for k in
                         ["ms_coherence", "ms_trace", "ms_candidates", "ms_refine", "ms_reduce"]}
     # roofline of the closest-hit kernel, the largest kernel of both steps:
-    # the group re-trace in coherent frames, the per-thread trace in full ones
+    # the group re-trace in coherent frames, the packet trace in full ones
     out["roofline"] = roofline(stats, "coherent" if main_mode == "coherent" else "full")
     if "full" in res and main_mode != "full":
         out["roofline_full_trace"] = roofline(res["full"][2], "full")

@@ -224,8 +224,8 @@ typedef struct dcem_frame_stats {
   int64_t captures;          /* capture records (reused + new) */
   int64_t unique_candidates; /* unique (tx, rx, order, faces) keys */
   int64_t valid_paths;
-  int64_t nodes_visited;     /* 4-wide BVH nodes the closest-hit traversal fetched from device memory
-                                (the per-thread traversal keeps the top three levels in LDS) */
+  int64_t nodes_visited;     /* 4-wide BVH nodes the closest-hit traversal fetched: one per node a
+                                packet of rays or a ray by itself enters */
   int64_t tri_tests;         /* ray-triangle tests of the closest-hit traversal */
   int32_t rebuilt;           /* last dcem_refit_bvh: DCEM_REFITTED, DCEM_REBUILT_FULL or DCEM_REBUILT_SUBTREES */
   int32_t coherent;          /* this frame reused the cache */
@@ -234,7 +234,7 @@ typedef struct dcem_frame_stats {
    * stages; in a coherent frame the refit shares the revalidation launch, so
    * ms_refit is that launch and ms_coherence includes it */
   float ms_refit, ms_coherence, ms_trace, ms_candidates, ms_refine, ms_reduce;
-  int32_t trace_kernel;      /* closest-hit traversal used: 0 one thread per ray, 1 one wavefront per ray */
+  int32_t trace_kernel;      /* closest-hit traversal used: 0 packets of rays, 1 a group of lanes per ray */
 } dcem_frame_stats;
 
 /* Source of a context's device memory, so that a framework (a caching
@@ -264,8 +264,8 @@ const char* dcem_last_error(const dcem_ctx* ctx);
  * DCEM_ERR_CAPTURES. */
 dcem_status dcem_set_capture_capacity(dcem_ctx* ctx, int64_t max_captures);
 /* Cap the closest-hit traversal stacks at `entries` entries per query (0
- * restores the full depth: 64 per ray in the per-thread traversal, the first
- * 32 in LDS, 128 in the group traversal; larger values are clamped to those).  Results do not
+ * restores the full depth: 64 per packet, and per ray of a packet that has
+ * lost its coherence, 128 in the group traversal; larger values are clamped to those).  Results do not
  * change unless a stack overflows; an overflow drops the entries that do not
  * fit, sets DCEM_ERR_STACK, and is reported as DCEM_E_CAPACITY by the next
  * synchronising call (that frame's outputs are undefined).  The full depth
@@ -480,7 +480,7 @@ typedef struct dcem_batch dcem_batch;
 /* Launch shape and tuning state of a batch. */
 typedef struct dcem_batch_info {
   int32_t n_ctx;
-  int32_t lds_stack;       /* per-thread traversal stack entries kept in LDS (16 or 32; the rest in device memory) */
+  int32_t lds_stack;       /* per-ray traversal stack entries kept in LDS (16 or 32; the rest in device memory) */
   int32_t blocks_per_cu;   /* persistent blocks of 128 threads per compute unit */
   int32_t chunk;           /* work items per queue chunk */
   int32_t tuned;           /* the shape comes from dcem_batch_tune */

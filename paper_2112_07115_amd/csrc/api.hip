@@ -143,11 +143,12 @@ hipError_t upload(DevBuf& b, const std::vector<T>& v, hipStream_t s) {
 
 bool mem_kind_ok(int k) { return k == DCEM_MEM_HOST || k == DCEM_MEM_DEVICE; }
 
-// Binary tree over the capture spheres (median split on the longest axis of the
-// centres), in the scene BVH's node layout; leaves are receiver ids and every
-// box is the sphere box grown by `grow`, so the box test is conservative.
+// Tree over the capture spheres (median splits on the longest axis of the
+// centres, two levels per node), in the traversals' 4-wide node layout; leaves
+// are receiver ids and every box is the sphere box grown by the padding, so
+// the box test is conservative.
 struct RxTree {
-  std::vector<Node> nodes;
+  std::vector<Node4> nodes;
   const std::vector<float>* rx;
   float r;
 
@@ -159,14 +160,8 @@ struct RxTree {
         hi[a] = std::max(hi[a], (*rx)[3 * ids[i] + a] + r);
       }
   }
-  static void set_slot(Node& n, int slot, const float* lo, const float* hi) {
-    float* f = reinterpret_cast<float*>(&n);
-    for (int a = 0; a < 3; ++a) { f[6 * slot + a] = lo[a]; f[6 * slot + 3 + a] = hi[a]; }
-  }
-  int build(std::vector<int>& ids, int b, int e) {
-    if (e - b == 1) return ~ids[b];
-    const int me = (int)nodes.size();
-    nodes.push_back(Node{});
+  // Order ids [b, e) by their median on the longest axis; the split position.
+  int split(std::vector<int>& ids, int b, int e) const {
     float lo[3], hi[3];
     box_of(ids, b, e, lo, hi);
     int ax = 0;
@@ -177,13 +172,33 @@ struct RxTree {
       const float px = (*rx)[3 * x + ax], py = (*rx)[3 * y + ax];
       return px < py || (px == py && x < y);
     });
-    const int l = build(ids, b, mid), rr = build(ids, mid, e);
-    float llo[3], lhi[3], rlo[3], rhi[3];
-    box_of(ids, b, mid, llo, lhi);
-    box_of(ids, mid, e, rlo, rhi);
-    set_slot(nodes[me], 0, llo, lhi);
-    set_slot(nodes[me], 1, rlo, rhi);
-    nodes[me].c = make_int4(l, rr, -1, 0);
+    return mid;
+  }
+  int build(std::vector<int>& ids, int b, int e) {
+    const int me = (int)nodes.size();
+    nodes.push_back(Node4{});
+    int cut[5] = {b, e, e, e, e}, n = 1;
+    if (e - b > 1) {
+      const int mid = split(ids, b, e);
+      n = 0;
+      for (const auto& h : {std::make_pair(b, mid), std::make_pair(mid, e)}) {
+        if (h.second - h.first > 1) cut[++n] = split(ids, h.first, h.second);
+        cut[++n] = h.second;
+      }
+    }
+    for (int s = 0; s < 4; ++s) {
+      Slot4 sl{};
+      sl.child = kEmpty;
+      sl.lx = sl.ly = sl.lz = sl.hx = sl.hy = sl.hz = INFINITY;
+      if (s < n) {
+        float lo[3], hi[3];
+        box_of(ids, cut[s], cut[s + 1], lo, hi);
+        sl.lx = lo[0]; sl.ly = lo[1]; sl.lz = lo[2];
+        sl.hx = hi[0]; sl.hy = hi[1]; sl.hz = hi[2];
+        sl.child = cut[s + 1] - cut[s] == 1 ? ~ids[cut[s]] : build(ids, cut[s], cut[s + 1]);
+      }
+      nodes[me].s[s] = sl;
+    }
     return me;
   }
 };
@@ -222,7 +237,7 @@ hipError_t upload_rx_columns(dcem_ctx* c, const std::vector<float>& rx) {
   return upload(c->rx_cols, rec, c->stream);
 }
 
-std::vector<Node> build_rx_tree(const std::vector<float>& rx, float radius) {
+std::vector<Node4> build_rx_tree(const std::vector<float>& rx, float radius) {
   RxTree t;
   t.rx = &rx;
   double R = 1.0;
@@ -231,15 +246,6 @@ std::vector<Node> build_rx_tree(const std::vector<float>& rx, float radius) {
   const int n = (int)(rx.size() / 3);
   std::vector<int> ids(n);
   for (int i = 0; i < n; ++i) ids[i] = i;
-  if (n == 1) {
-    Node root{};
-    float lo[3], hi[3];
-    t.box_of(ids, 0, 1, lo, hi);
-    RxTree::set_slot(root, 0, lo, hi);
-    RxTree::set_slot(root, 1, lo, hi);
-    root.c = make_int4(~0, ~0, -1, 0);
-    return {root};
-  }
   t.build(ids, 0, n);
   return t.nodes;
 }
@@ -911,7 +917,7 @@ dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan
   if (need_dirs) HIP_TRY(upload(c->src_pos, srch, c->stream), "upload sources");   // sources or rays changed
   if (need_rx) {
     HIP_TRY(upload(c->tgt_pos, tgth, c->stream), "upload targets");
-    std::vector<Node> rt = build_rx_tree(tgth, p->rx_radius);
+    const std::vector<Node4> rt = build_rx_tree(tgth, p->rx_radius);
     c->n_rx_nodes = (int32_t)rt.size();
     HIP_TRY(upload(c->rx_nodes, rt, c->stream), "upload capture-sphere tree");
     HIP_TRY(upload_rx_columns(c, tgth), "upload capture-sphere columns");
@@ -1023,6 +1029,7 @@ dcem_status frame_front(dcem_ctx* c, const FramePlan& plan) {
 dcem_status frame_trace(dcem_ctx* c, const FramePlan& plan) {
   ev_record(c, 8);
   if (plan.recapture && plan.n_work > 0) launch_recapture(c);
+  c->count_blocks = 0;
   const int traversal =
       plan.n_work > 0 ? launch_trace(c, !plan.coherent, plan.keep_cache, plan.expected, plan.n_prev) : 0;
   if (traversal < 0) return fail(c, DCEM_E_OUT_OF_MEMORY, "alloc traversal stack");
@@ -1513,6 +1520,7 @@ dcem_status batch_frame(dcem_batch* b, const dcem_trace_params* params, const dc
     if (e != hipSuccess) st = hip_fail(c, e, "batched trace");
     for (dcem_ctx* f : full) {
       f->last_trace_kernel = 0;
+      f->count_blocks = 0;   // added to the counters by the batched trace
       ev_record(f, 2);
     }
   }

@@ -516,12 +516,13 @@ __global__ void k_collapse(const Node* __restrict__ nodes, const float* __restri
     if (e < m) {
       sl.lx = lo[e][0]; sl.ly = lo[e][1]; sl.lz = lo[e][2];
       sl.hx = hi[e][0]; sl.hy = hi[e][1]; sl.hz = hi[e][2];
-      sl.child = ch[e];
+      sl.child = ch[e] >= 0 ? ch[e] : ~(4 * q + e);
       sl.mask = (kids >> (4 * e)) & 15u;
     } else {
-      sl.lx = sl.ly = sl.lz = sl.hx = sl.hy = sl.hz = 0.0f;
+      sl.lx = sl.ly = sl.lz = sl.hx = sl.hy = sl.hz = INFINITY;
       sl.child = kEmpty;
       sl.mask = 0;
+      tri4[4 * (size_t)q + e] = Leaf{};   // a triangle without area: no ray hits it
     }
   }
   if (q == 0) info[1] = own;

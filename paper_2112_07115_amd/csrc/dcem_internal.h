@@ -14,10 +14,9 @@ namespace dcem {
 constexpr int kWave = 64;
 constexpr float kTMin = 1e-4f;           // hits closer than this to a segment start are ignored
 constexpr double kTMinD = 1e-4;
-constexpr int kStackLds = 32;            // per-thread traversal stack entries kept in LDS
-constexpr int kStackSpill = 32;          // further entries per thread in device memory (rarely reached)
+constexpr int kStackLds = 32;            // traversal stack entries of a thread of k_recapture kept in LDS
+constexpr int kStackSpill = 32;          // its further entries in device memory (rarely reached)
 constexpr int kStackSize = kStackLds + kStackSpill;
-constexpr int kTopNodes = 21;            // 4-wide nodes of the top three levels, kept in LDS
 constexpr int kTraceBlock = 128;         // threads per trace block
 constexpr uint32_t kNoRay = 0xffffffffu;
 constexpr int32_t kTransmit = 1 << 30;   // decoded face entry: the interaction transmits through the face
@@ -33,7 +32,7 @@ struct __align__(16) Node {
 };
 
 // One child slot of a 4-wide node, 32 bytes: the child's box, the child
-// entry (>= 0 node, < 0 leaf ~entry, kEmpty unused) and, for a child node, its
+// entry (>= 0 node, < 0 leaf slot ~entry, kEmpty unused: its box at infinity) and, for a child node, its
 // leaf-slot mask (bit j set: slot j of that child is a leaf).
 struct __align__(16) Slot4 {
   float lx, ly, lz;
@@ -187,7 +186,7 @@ struct dcem_ctx {
   int32_t n_internal = 0;
   double sah_build = 0.0, sah_last = 1.0;
   int32_t last_rebuilt = 0;
-  int32_t last_trace_kernel = 0;                     // traversal of the last frame (0 per thread, 1 per wavefront)
+  int32_t last_trace_kernel = 0;                     // traversal of the last frame (0 packets, 1 groups)
   dcem::DevBuf nodes, leaf_slot, leaf_tri, leaf_parent, refit_cnt, morton, sort_tmp, sah_part, scene_box,
       node_range;
   dcem::DevBuf nodes4, bvh2_of4, map4, depth_key;   // 4-wide tree and its mapping from the binary one
@@ -211,7 +210,7 @@ struct dcem_ctx {
   int32_t n_src = 0, n_tgt = 0;
   bool backward = false;
   // rx_nodes, rx_cols: the capture spheres (the targets) as a tree and by x column
-  dcem::DevBuf dirs, ray_order, src_pos, tgt_pos, freqs, rx_nodes;
+  dcem::DevBuf dirs, dirs_by_pos, ray_order, src_pos, tgt_pos, freqs, rx_nodes;
   // targets ordered by x column: [n_tgt] float4 (x, y, z, target index
   // bits), then kRxCols + 1 int32 column starts; column of x:
   // clamp(floor((x - rx_col_x0) * rx_col_scale), 0, kRxCols - 1)
@@ -229,6 +228,9 @@ struct dcem_ctx {
   dcem::DevBuf caps[2];      // double-buffered capture lists
   int cur_caps = 0;
   dcem::DevBuf work_list, invalid_flag;   // re-trace list; per-ray first invalid segment (255 = valid)
+  dcem::DevBuf queues;       // chunk queues of the packet trace
+  dcem::DevBuf count_part;   // item counts of each block of the last trace launch, added up by the reduction
+  int count_blocks = 0;      // its blocks (0: the counters were added to directly)
   dcem::DevBuf stack_spill;  // per-thread traversal stack entries beyond the LDS part (kStackSpill each)
   // One device block holding everything the host reads after a frame, copied
   // in one transfer to pinned host memory: counters (128 B), error word
@@ -291,8 +293,8 @@ struct dcem_ctx {
             &face_tri_off, &face_tris, &face_ref_tri, &xf, &obj_box, &face_plane, &tri_slot, &face_slots,
             &nodes, &leaf_slot, &leaf_tri, &leaf_parent, &refit_cnt, &morton, &sort_tmp, &sah_part, &scene_box,
             &node_range, &nodes4, &bvh2_of4, &map4, &depth_key, &slot4, &cross, &tree_info, &tri4, &face_build,
-            &dirs, &ray_order, &src_pos, &tgt_pos, &freqs, &rx_nodes, &rx_cols, &grad_buf, &face_log, &ray_state,
-            &seg_o, &seg_d, &log_tri, &log_t, &log_len, &caps[0], &caps[1], &work_list, &invalid_flag, &stack_spill,
+            &dirs, &dirs_by_pos, &ray_order, &src_pos, &tgt_pos, &freqs, &rx_nodes, &rx_cols, &grad_buf, &face_log, &ray_state,
+            &seg_o, &seg_d, &log_tri, &log_t, &log_len, &caps[0], &caps[1], &work_list, &invalid_flag, &stack_spill, &queues, &count_part,
             &frame_block, &cand_keys, &cand_perm, &cand_tmp, &uniq_idx, &first_ray, &path_valid, &path_len,
             &path_tau, &path_aod, &path_aoa, &path_amp, &pair_range, &path_order, &path_faces, &path_pts,
             &sort_hist, &series_buf, &expand_buf, &face_pen, &mat_pen, &branch_set};

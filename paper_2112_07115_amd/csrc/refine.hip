@@ -1350,7 +1350,20 @@ __device__ inline void wave_run(const int32_t* __restrict__ a, int n, int key, i
 __global__ __launch_bounds__(256) void k_reduce(const int32_t* __restrict__ pair, const uint8_t* __restrict__ valid,
                                                 const double* __restrict__ amp, const uint32_t* __restrict__ n_unique,
                                                 int n_pairs, int n_freqs, double* __restrict__ p_coh,
-                                                double* __restrict__ p_inc, uint32_t* __restrict__ counters) {
+                                                double* __restrict__ p_inc, uint32_t* __restrict__ counters,
+                                                const uint32_t* __restrict__ count_part, int count_blocks) {
+  // the trace's item counts (segments, nodes, triangle tests), added up by
+  // three wavefronts of the last block
+  if (count_blocks > 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x < 3 * kWave) {
+    const int q = threadIdx.x / kWave;
+    unsigned long long s = 0;
+    for (int b = threadIdx.x & (kWave - 1); b < count_blocks; b += kWave) s += count_part[3 * b + q];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+      if (q == 0) counters[kCntSegments] = (uint32_t)s;
+      else *reinterpret_cast<unsigned long long*>(&counters[q == 1 ? kCntNodes : kCntTris]) = s;
+    }
+  }
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   // the re-trace has read this frame's list length: zero it for the next
@@ -1937,7 +1950,7 @@ void launch_reduce(dcem_ctx* c) {
   hipLaunchKernelGGL(k_reduce, dim3((n_pairs * 64 + 255) / 256), dim3(256), 0, c->stream,
                      ptr<int32_t>(c->pair_range), ptr<uint8_t>(c->path_valid), ptr<double>(c->path_amp),
                      c->cnt_dev + kCntUnique, n_pairs, c->n_freqs, c->pcoh_dev,
-                     c->pinc_dev, c->cnt_dev);
+                     c->pinc_dev, c->cnt_dev, ptr<uint32_t>(c->count_part), c->count_blocks);
 }
 
 }  // namespace dcem

@@ -55,18 +55,11 @@ __device__ inline void setup_ray(Ray& r) {
 // one is exactly zero.  Edge functions are evaluated without FMA contraction
 // so that two triangles sharing an edge compute exactly opposite values.
 // Returns the hit distance t (IEEE division) or -1.  The axis permutation is
-// read through a policy: the ray's axis indices (per-thread traversal) or
-// per-lane select masks precomputed once per segment (group traversal); the
-// arithmetic is the same.
-struct RayAxes {
-  int kx, ky, kz;
-  __device__ float x(const float3& v) const { return comp(v, kx); }
-  __device__ float y(const float3& v) const { return comp(v, ky); }
-  __device__ float z(const float3& v) const { return comp(v, kz); }
-};
-
+// applied by per-lane select masks, made once per segment.
+//
 // Component selection by bit masks (all ones for the chosen component), so
-// that lanes tracing different rays need no branches.
+// that lanes tracing different rays need no branches: selection by index compiles to
+// about 150 scalar instructions of branches per triangle.
 struct MaskAxes {
   uint32_t x0, x1, x2, y0, y1, y2, z0, z1, z2;
   __device__ static float pick(const float3& v, uint32_t m0, uint32_t m1, uint32_t m2) {
@@ -77,8 +70,13 @@ struct MaskAxes {
   __device__ float z(const float3& v) const { return pick(v, z0, z1, z2); }
 };
 
-template <class Axes>
-__device__ inline float watertight_axes(const Ray& r, const Axes& ax, const float4& p0, const float4& p1,
+__device__ inline MaskAxes mask_axes(const Ray& r) {
+  auto m = [](int k, int j) { return k == j ? 0xffffffffu : 0u; };
+  return MaskAxes{m(r.kx, 0), m(r.kx, 1), m(r.kx, 2), m(r.ky, 0), m(r.ky, 1),
+                  m(r.ky, 2), m(r.kz, 0), m(r.kz, 1), m(r.kz, 2)};
+}
+
+__device__ inline float watertight(const Ray& r, const MaskAxes& ax, const float4& p0, const float4& p1,
                                         const float4& p2) {
 #pragma clang fp contract(off)
   const float3 A = make_float3(p0.x - r.o.x, p0.y - r.o.y, p0.z - r.o.z);
@@ -103,10 +101,6 @@ __device__ inline float watertight_axes(const Ray& r, const Axes& ax, const floa
   return __fdiv_rn(T, det);
 }
 
-__device__ inline float watertight(const Ray& r, const float4& p0, const float4& p1, const float4& p2) {
-  return watertight_axes(r, RayAxes{r.kx, r.ky, r.kz}, p0, p1, p2);
-}
-
 // Conservative slab test against a box given as (lo, hi) over (t0, tmax].
 __device__ inline bool slab(const Ray& r, float lx, float ly, float lz, float hx, float hy, float hz, float tmax,
                             float& tnear) {
@@ -127,20 +121,11 @@ struct Hit {
   int face;
 };
 
-__device__ inline void test_leaf(const Ray& r, const Leaf* __restrict__ tri4, int li, int excl, Hit& h) {
-  const float4 p0 = tri4[li].v0, p1 = tri4[li].v1, p2 = tri4[li].v2;
-  const int face = __float_as_int(p1.w);
-  if (face == excl) return;
-  const float t = watertight(r, p0, p1, p2);
-  if (!(t > kTMin)) return;
-  const int tri = __float_as_int(p0.w);
-  if (t < h.t || (t == h.t && tri < h.tri)) {
-    h.t = t;
-    h.tri = tri;
-    h.leaf = li;
-    h.face = face;
-  }
-}
+// Finite limit of a box's entry distance.  Empty slots' boxes lie at infinity,
+// so the traversals of the scene do not look for their code (doing so costs
+// 1.12x on the urban frame); a ray of infinite or undefined direction that
+// "meets" one finds a triangle without area there.
+constexpr float kFarthest = 3.4e38f;
 
 __device__ inline void cswap(float& ta, int& ca, float& tb, int& cb) {
   if (tb < ta) {
@@ -149,7 +134,7 @@ __device__ inline void cswap(float& ta, int& ca, float& tb, int& cb) {
   }
 }
 
-// Per-thread traversal stack: the first kStackLds entries in LDS (strided by
+// Per-thread traversal stack: the first lds_entries entries in LDS (strided by
 // the block size), deeper ones in this thread's region of device memory.  A
 // 4-wide traversal pushes at most three entries per level, so the spill part
 // is reached only by rays in unusually deep parts of a tree.
@@ -158,84 +143,21 @@ struct ThreadStack {
   int* spill;           // this thread's first spill entry
   size_t spill_stride;  // threads of the grid
   int cap;              // entries usable (<= kStackSize)
-  int lds_entries = kStackLds;
+  int lds_entries;      // entries in LDS
+  int lds_stride;       // threads of the block
   __device__ void put(int i, int v) {
-    if (i < lds_entries) lds[i * kTraceBlock] = v;
+    if (i < lds_entries) lds[i * lds_stride] = v;
     else spill[(size_t)(i - lds_entries) * spill_stride] = v;
   }
   __device__ int get(int i) const {
-    return i < lds_entries ? lds[i * kTraceBlock] : spill[(size_t)(i - lds_entries) * spill_stride];
+    return i < lds_entries ? lds[i * lds_stride] : spill[(size_t)(i - lds_entries) * spill_stride];
   }
 };
 
-typedef __attribute__((address_space(3))) const Node4 LdsNode4;      // a node in LDS
 typedef __attribute__((address_space(1))) const Node4 GlobalNode4;   // a node in device memory
-// Node i of an array known to live in LDS / in device memory (address-space
-// casts need C-style casts).
-__device__ inline Node4 node_in_lds(const Node4* a, int i) { return *(const Node4*)((const LdsNode4*)a + i); }
+// Node i of an array known to live in device memory (address-space casts need
+// C-style casts).
 __device__ inline Node4 node_in_memory(const Node4* a, int i) { return *(const Node4*)((const GlobalNode4*)a + i); }
-
-// Closest hit: lexicographic minimum of (t, triangle id) over all triangles
-// with t > t_min outside face `excl`, by a stack traversal of the 4-wide tree
-// (nearest child first; the top levels are read from LDS).  The result does
-// not depend on the tree shape: boxes are conservative and nodes are pruned
-// only when their entry distance exceeds the current best (ties are visited).
-__device__ Hit closest_hit(const Ray& r, const Node4* __restrict__ nodes, const Node4* top, int n_top, int n4,
-                           const Leaf* __restrict__ tri4, int excl, ThreadStack& stack, bool& overflow,
-                           uint32_t& n_nodes, uint32_t& n_tris) {
-  Hit h{FLT_MAX, -1, -1, -1};
-  if (n4 == 0) return h;
-  int node = 0, sp = 0;
-  // a sound tree visits each node at most once per query; the bound only
-  // guarantees termination
-  for (int64_t guard = (int64_t)n4 + 2;; --guard) {
-    if (guard == 0) { overflow = true; break; }
-    // read through address-space-typed pointers, in two branches: a select
-    // of the two pointers would make every node read a generic load that
-    // waits on both the LDS and the memory counters
-    Node4 nd;
-    if (node < n_top) nd = node_in_lds(top, node);
-    else nd = node_in_memory(nodes, node);
-    if (node >= n_top) ++n_nodes;   // fetched from memory (the top levels sit in LDS)
-    float t[4];
-    int c[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      t[e] = INFINITY;
-      c[e] = kEmpty;
-      const Slot4& sl = nd.s[e];
-      const int ch = sl.child;
-      if (ch == kEmpty) continue;
-      float tn;
-      if (!slab(r, sl.lx, sl.ly, sl.lz, sl.hx, sl.hy, sl.hz, h.t, tn)) continue;
-      if (ch < 0) {
-        test_leaf(r, tri4, 4 * node + e, excl, h);
-        ++n_tris;
-      } else {
-        t[e] = tn;
-        c[e] = ch;
-      }
-    }
-    cswap(t[0], c[0], t[1], c[1]);
-    cswap(t[2], c[2], t[3], c[3]);
-    cswap(t[0], c[0], t[2], c[2]);
-    cswap(t[1], c[1], t[3], c[3]);
-    cswap(t[1], c[1], t[2], c[2]);
-    if (c[0] == kEmpty) {
-      if (sp == 0) break;
-      node = stack.get(--sp);
-      continue;
-    }
-#pragma unroll
-    for (int e = 3; e >= 1; --e) {
-      if (c[e] == kEmpty) continue;
-      if (sp < stack.cap) stack.put(sp++, c[e]);
-      else overflow = true;
-    }
-    node = c[0];
-  }
-  return h;
-}
 
 // Fibonacci sphere in FP64, plain evaluation (no fused multiply-add), rounded to FP32.
 __global__ void k_fibonacci(float* __restrict__ dirs, int64_t n) {
@@ -253,11 +175,18 @@ __global__ void k_fibonacci(float* __restrict__ dirs, int64_t n) {
   dirs[3 * i + 2] = (float)z;
 }
 
+constexpr int kWaves = 4;                   // wavefronts per block of the group trace
+constexpr int kWaveBlock = kWaves * kWave;
+constexpr int kPacketBlock = 256;            // threads per block of k_trace_packet
+constexpr int kPacketPerSimd = 4;            // its wavefronts per SIMD, and so blocks per compute unit
+constexpr int kPacketStack = 16;             // per-lane traversal stack entries in LDS (16 KB)
+constexpr int kMinPacket = 4, kPacketWaves = 16;   // smallest packet; wavefronts per compute unit it keeps
+constexpr uint32_t kPacketTrial = 16, kPacketNum = 5, kPacketDen = 10;   // see incoherent()
 struct TraceArgs {
   const Node4* nodes4;
   const Leaf* tri4;           // leaf triangles in slot order
   const uint32_t* n4_dev;     // number of 4-wide nodes (null: empty scene)
-  const float* dirs;
+  const float* dirs;          // ray directions by traversal position
   const uint32_t* ray_order;  // traversal position -> ray (directions sorted along a space-filling curve);
                               // per-ray device state is indexed by position: neighbouring directions share
                               // cache lines
@@ -268,7 +197,7 @@ struct TraceArgs {
   const float* rx;
   int n_rx;
   int capture;          // 0: no capture tests (candidates come from the visited series)
-  const Node* rx_nodes; // BVH over the capture spheres (boxes padded), leaves = sphere ids
+  const Node4* rx_nodes; // 4-wide tree over the capture spheres (boxes padded), leaves = sphere ids
   int n_rx_nodes;
   float r2;
   float rx_zlo, rx_zhi; // z range of all capture spheres
@@ -278,6 +207,8 @@ struct TraceArgs {
   const uint8_t* restart;     // work-list mode: first segment to trace again
   int64_t n_rays;             // rays per source and branch
   int n_work;
+  int n_src;
+  uint32_t packet;            // rays per packet
   const uint32_t* work_list;  // null: all work items
   int K;                      // interactions at most (segments 0..K)
   // Transmission (the "Reflected and transmitted rays" item of Sec. III):
@@ -292,6 +223,7 @@ struct TraceArgs {
   const uint8_t* face_pen;
   const int32_t* face_object;
   uint32_t* counters;
+  uint32_t* queues;           // the trace's chunk queues (ChunkQueues)
   int32_t* face_log;          // [K+1][n_work]
   uint8_t* ray_state;         // [n_work]
   float4* seg_o;              // [K+1][n_work] or null
@@ -306,6 +238,7 @@ struct TraceArgs {
   uint32_t n_prev;
   int* stack_spill;           // [kStackSpill][grid threads] per-thread stack entries beyond the LDS part
   int stack_thread;           // stack entries a per-thread traversal may use (<= kStackSize)
+  uint32_t* count_part;       // [grid][3] item counts of each block (segments, nodes, triangle tests)
   int stack_group;            // stack entries a group traversal may use (<= kRayStack)
 };
 
@@ -380,139 +313,437 @@ __device__ inline void transmit_ray(Ray& r, float t) {
   setup_ray(r);
 }
 
+// May a segment from height za with z direction dz meet the capture spheres'
+// z range?  th: its hit distance (hit), else it is unbounded.
+__device__ inline bool in_rx_band(const TraceArgs& a, const Ray& r, bool hit, float th) {
+  const float za = r.o.z;
+  const float zb = hit ? __fmaf_rn(th, r.d.z, r.o.z) : (r.d.z > 0 ? INFINITY : (r.d.z < 0 ? -INFINITY : r.o.z));
+  return fmaxf(za, zb) >= a.rx_zlo && fminf(za, zb) <= a.rx_zhi;
+}
+
+// Append the capture of sphere c by segment k of work item `work`.
+__device__ inline void add_capture(const TraceArgs& a, uint32_t work, uint32_t txi, int c, int k, bool& cap_over) {
+  const uint32_t slot = atomicAdd(&a.counters[kCntCaptures], 1u);
+  if (slot < a.cap_capacity) {
+    Capture cp;
+    cp.work = work;
+    cp.pair_order = ((txi * (uint32_t)a.n_rx + (uint32_t)c) << 4) | (uint32_t)k;
+    a.caps[slot] = cp;
+  } else {
+    cap_over = true;
+  }
+}
+
 // Captures of one segment [o, o + tend d] (tend infinite on a miss; th its
-// hit distance): receivers whose padded box the segment meets, by the
-// receiver tree, then the exact closest-approach test; records appended to
-// the frame's capture list.
+// hit distance): capture spheres whose padded box the segment meets, by their
+// 4-wide tree, then the exact closest-approach test; records appended to the
+// frame's capture list.
 __device__ void capture_segment(const TraceArgs& a, const Ray& r, bool hit, float th, float tend, float dd,
                                 uint32_t work, uint32_t txi, int k, ThreadStack& stack, bool& overflow,
                                 bool& cap_over) {
   if (!a.capture) return;
-  const float za = r.o.z;
-  const float zb = hit ? __fmaf_rn(th, r.d.z, r.o.z) : (r.d.z > 0 ? INFINITY : (r.d.z < 0 ? -INFINITY : r.o.z));
-  if (fmaxf(za, zb) >= a.rx_zlo && fminf(za, zb) <= a.rx_zhi) {
-    int node = 0, sp = 0;
-    for (int guard = 2 * a.n_rx_nodes + 2; guard > 0; --guard) {
-      const Node nd = a.rx_nodes[node];
-      float t0, t1;
-      bool h0 = slab(r, nd.b0.x, nd.b0.y, nd.b0.z, nd.b0.w, nd.b1.x, nd.b1.y, tend, t0);
-      bool h1 = slab(r, nd.b1.z, nd.b1.w, nd.b2.x, nd.b2.y, nd.b2.z, nd.b2.w, tend, t1);
-      const int c0 = nd.c.x, c1 = nd.c.y;
-      for (int side = 0; side < 2; ++side) {
-        const int cc = side ? c1 : c0;
-        const bool hh = side ? h1 : h0;
-        if (!(hh && cc < 0) || (side == 1 && c1 == c0)) continue;   // a lone sphere fills both slots
-        const int c = ~cc;
-        if (captured(r, tend, dd, a.rx[3 * c], a.rx[3 * c + 1], a.rx[3 * c + 2], a.r2)) {
-          const uint32_t slot = atomicAdd(&a.counters[kCntCaptures], 1u);
-          if (slot < a.cap_capacity) {
-            Capture cp;
-            cp.work = work;
-            cp.pair_order = ((txi * (uint32_t)a.n_rx + (uint32_t)c) << 4) | (uint32_t)k;
-            a.caps[slot] = cp;
-          } else {
-            cap_over = true;
-          }
-        }
-      }
-      h0 = h0 && c0 >= 0;
-      h1 = h1 && c1 >= 0;
-      if (h0 && h1) {
-        if (sp < stack.cap) stack.put(sp++, c1);
-        else overflow = true;
-        node = c0;
-      } else if (h0) {
-        node = c0;
-      } else if (h1) {
-        node = c1;
+  if (!in_rx_band(a, r, hit, th)) return;
+  int node = 0, sp = 0;
+  for (int guard = a.n_rx_nodes + 2; guard > 0; --guard) {
+    const Node4 nd = node_in_memory(a.rx_nodes, node);
+    int next = -1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int ch = nd.s[e].child;
+      float tn;
+      if (ch == kEmpty || !slab(r, nd.s[e].lx, nd.s[e].ly, nd.s[e].lz, nd.s[e].hx, nd.s[e].hy, nd.s[e].hz, tend, tn))
+        continue;
+      if (ch < 0) {
+        const int c = ~ch;
+        if (captured(r, tend, dd, a.rx[3 * c], a.rx[3 * c + 1], a.rx[3 * c + 2], a.r2))
+          add_capture(a, work, txi, c, k, cap_over);
+      } else if (next < 0) {
+        next = ch;
+      } else if (sp < stack.cap) {
+        stack.put(sp++, ch);
       } else {
-        if (sp == 0) break;
-        node = stack.get(--sp);
+        overflow = true;
       }
     }
+    if (next < 0) {
+      if (sp == 0) break;
+      next = stack.get(--sp);
+    }
+    node = next;
   }
 }
 
-// Per-thread tracing of one work item (a ray, from its first segment or, in
-// work-list mode, from its restart segment): closest hits, captures,
-// reflections, the per-bounce face log and segment cache.
+// Counts and error flags of a thread, summed into the frame's counters.
 struct ItemCounts {
   uint32_t seg = 0, node = 0, tri = 0;
   bool overflow = false, cap_over = false;
 };
 
-__device__ void trace_item(const TraceArgs& a, uint32_t wi, const Node4* top, int n_top, int n4, ThreadStack& stack,
-                           ItemCounts& ic) {
-  uint32_t& seg_count = ic.seg;
-  uint32_t& node_count = ic.node;
-  uint32_t& tri_count = ic.tri;
-  bool& overflow = ic.overflow;
-  bool& cap_over = ic.cap_over;
-  // work: the ray's traversal position (its index in the face log, the
-  // caches and the capture records); rid: its ray id (the parity log)
-  const uint32_t work = a.work_list ? a.work_list[wi] : wi;
-  const uint32_t vsrc = (uint32_t)(work / (uint64_t)a.n_rays);   // src * n_branch + branch
-  const uint32_t ray = a.ray_order[work - (uint64_t)vsrc * a.n_rays];
-  const uint32_t rid = vsrc * (uint32_t)a.n_rays + ray;
-  const uint32_t txi = vsrc / (uint32_t)a.n_branch;
+// Chunks of work for the wavefronts of a persistent launch.  The chunks are
+// cut into one part per XCD, each with a queue on a cache line of its own: an
+// XCD's blocks (consecutive blocks go to consecutive XCDs) take their part's
+// first chunks by position, then its others off its queue, then help with the
+// other parts.  One address takes only about 90 atomics per microsecond from
+// the whole chip, so a single queue would bound a launch of 16384 chunks to
+// 190 us.  (Asking for the next chunk ahead of the work on the current one hides
+// the round trip but ties chunks to slow wavefronts: 503 us for 390 us.)
+constexpr int kXcds = 8;
+constexpr int kQueueStride = 32;   // words between the queues' counters
+
+struct ChunkQueues {
+  uint32_t* counter;   // [kXcds] at kQueueStride
+  uint32_t n_chunks;
+  int part, tries;     // this wavefront's part; parts found empty
+  uint32_t asked;      // the chunk to come: an answer of part (part + tries)'s queue (in lane 0)
+  bool first;          // or this wavefront's first chunk, by position
+  __device__ ChunkQueues(uint32_t* c, uint32_t n) : counter(c), n_chunks(n), tries(0), first(true) {
+    part = blockIdx.x % kXcds;
+    asked = threadIdx.x / kWave * blocks(part) + blockIdx.x / kXcds;
+  }
+  __device__ static uint32_t blocks(int q) { return (gridDim.x + kXcds - 1 - q) / kXcds; }
+  __device__ uint32_t begin(int q) const { return (uint32_t)((uint64_t)n_chunks * q / kXcds); }
+  // the part's first chunk that is not some wavefront's first
+  __device__ uint32_t queued(int q) const { return begin(q) + blocks(q) * (blockDim.x / kWave); }
+  __device__ void ask() {
+    if ((threadIdx.x & (kWave - 1)) == 0)
+      asked = atomicAdd(counter + (part + tries) % kXcds * kQueueStride, 1u);
+  }
+  // The next chunk (false: none is left).
+  __device__ bool chunk(uint32_t& c) {
+    if (!first) ask();
+    while (tries < kXcds) {
+      const int q = (part + tries) % kXcds;
+      c = (first ? begin(q) : queued(q)) + __builtin_amdgcn_readfirstlane(asked);
+      if (c < begin(q + 1)) {
+        first = false;
+        return true;
+      }
+      // this part is empty: the next one with chunks left (a counter only grows)
+      do {
+        ++tries;
+      } while (tries < kXcds && left((part + tries) % kXcds) == 0);
+      first = false;
+      if (tries < kXcds) ask();
+    }
+    return false;
+  }
+  __device__ uint32_t left(int q) const {
+    const uint32_t n = begin(q + 1) - min(begin(q + 1), queued(q));
+    if (n == 0) return 0;
+    const uint32_t i = __hip_atomic_load(counter + q * kQueueStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __builtin_amdgcn_readfirstlane(n - min(i, n));
+  }
+};
+
+// Closest hit of one lane's ray by a stack traversal of its own, nearest child
+// first, from the best hit so far.
+__device__ __forceinline__ void lane_walk(const TraceArgs& a, const Ray& r, int n4, int excl, ThreadStack& stack, Hit& h,
+                                          ItemCounts& ic) {
+  int node = 0, sp = 0;
+  const MaskAxes ax = mask_axes(r);
+  // a sound tree visits each node at most once per query; the bound only
+  // guarantees termination
+  for (int guard = n4 + 2; guard > 0; --guard) {
+    const Node4 nd = node_in_memory(a.nodes4, node);
+    ++ic.node;
+    float t[4];
+    int c[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const Slot4& sl = nd.s[e];
+      float tn;
+      t[e] = INFINITY;
+      c[e] = sl.child;
+      if (!slab(r, sl.lx, sl.ly, sl.lz, sl.hx, sl.hy, sl.hz, fminf(h.t, kFarthest), tn)) continue;
+      if (sl.child < 0) {
+        const Leaf l = a.tri4[4 * node + e];
+        const int face = __float_as_int(l.v1.w), tri = __float_as_int(l.v0.w);
+        const float tt = watertight(r, ax, l.v0, l.v1, l.v2);
+        ic.tri += face != excl ? 1u : 0u;
+        if (face != excl && tt > kTMin && (tt < h.t || (tt == h.t && tri < h.tri))) h = Hit{tt, tri, 4 * node + e, face};
+      } else {
+        t[e] = tn;
+      }
+    }
+    cswap(t[0], c[0], t[1], c[1]);
+    cswap(t[2], c[2], t[3], c[3]);
+    cswap(t[0], c[0], t[2], c[2]);
+    cswap(t[1], c[1], t[3], c[3]);
+    cswap(t[1], c[1], t[2], c[2]);
+#pragma unroll
+    for (int e = 3; e >= 1; --e) {
+      if (!(t[e] < INFINITY)) continue;
+      if (sp < stack.cap) stack.put(sp++, c[e]);
+      else ic.overflow = true;
+    }
+    if (t[0] < INFINITY) node = c[0];
+    else if (sp > 0) node = stack.get(--sp);
+    else return;
+  }
+  ic.overflow = true;
+}
+
+typedef __attribute__((address_space(4))) const Node4 UniformNode4;   // read by scalar loads
+typedef __attribute__((address_space(4))) const Leaf UniformLeaf;
+typedef __attribute__((address_space(4))) const float UniformFloat;
+
+__device__ inline Node4 uniform_node(const Node4* a, int i) { return *(const Node4*)((const UniformNode4*)a + i); }
+
+// One step order for a packet's children: nearest first by the entry distance
+// of each child's first lane (distances are not negative: their bits order
+// like the values; kNone sorts last).
+struct PacketOrder {
+  uint32_t t[4];
+  int c[4];
+  __device__ void swap(int i, int j) {
+    if (t[j] < t[i]) {
+      const uint32_t x = t[i]; t[i] = t[j]; t[j] = x;
+      const int y = c[i]; c[i] = c[j]; c[j] = y;
+    }
+  }
+};
+
+// The stack of a packet: one register over the wavefront's lanes.
+struct PacketStack {
+  int v = 0, n = 0;
+  __device__ void push(int x) { v = (int)(threadIdx.x & (kWave - 1)) == n ? x : v; ++n; }
+  __device__ int pop() { return __builtin_amdgcn_readlane(v, --n); }
+};
+
+// A packet pays while the lanes in the nodes it enters are more than kPacketNum
+// / kPacketDen of the rays alive.  (Shares of 0.3, 0.4, 0.5, 0.6 and 0.7: 370,
+// 345, 342, 343 and 340 us on the urban frame, 707, 710, 707, 725 and 728 on the
+// office, 40, 40, 40, 43 and 43 on the toy scene.)
+__device__ inline bool incoherent(uint32_t entered, uint32_t lanes, int live) {
+  return kPacketDen * lanes < kPacketNum * entered * (uint32_t)live;
+}
+
+// Walk a 4-wide tree with the wavefront's 64 rays together: a node is entered
+// when any lane's ray meets its box before that lane's limit tmax(), and its
+// leaves go to leaf(slot, child, in) with in set for the lanes that meet the
+// leaf's box.  Lanes whose limit is negative take no part.  Nodes are read by
+// scalar loads and control is uniform: no lane waits for another's stack, and
+// a box test costs what one lane's would.  Ends early, returning false, once it
+// has entered kPacketTrial nodes with too few of the `live` lanes in each.
+template <class Limit, class LeafTest>
+__device__ __forceinline__ bool packet_walk(const Node4* nodes, const Ray& r, int live, int cap, bool& overflow,
+                                            uint32_t& entered, uint32_t& lanes, Limit tmax, LeafTest leaf) {
+  constexpr uint32_t kNone = 0xffffffffu;
+  PacketStack stack;
+  int node = 0;
+  entered = lanes = 0;
+  while (true) {
+    if (++entered > kPacketTrial && incoherent(entered, lanes, live)) return false;
+    const Node4 nd = uniform_node(nodes, node);
+    uint64_t m[4], any = 0;
+    float tn[4];
+    bool in[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const Slot4& sl = nd.s[e];
+      in[e] = slab(r, sl.lx, sl.ly, sl.lz, sl.hx, sl.hy, sl.hz, tmax(), tn[e]);
+      m[e] = __ballot(in[e]);
+      any |= m[e];
+    }
+    PacketOrder o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o.t[e] = kNone;
+      o.c[e] = nd.s[e].child;
+      if (m[e] == 0) continue;
+      if (o.c[e] < 0) leaf(4 * node + e, o.c[e], in[e]);
+      else o.t[e] = (uint32_t)__builtin_amdgcn_readlane(__float_as_int(tn[e]), __ffsll((unsigned long long)m[e]) - 1);
+    }
+    lanes += (uint32_t)__popcll(any);
+    o.swap(0, 1);
+    o.swap(2, 3);
+    o.swap(0, 2);
+    o.swap(1, 3);
+    o.swap(1, 2);
+#pragma unroll
+    for (int e = 3; e >= 1; --e) {
+      if (o.t[e] == kNone) continue;
+      if (stack.n < cap) stack.push(o.c[e]);
+      else overflow = true;
+    }
+    if (o.t[0] != kNone) node = o.c[0];
+    else if (stack.n > 0) node = stack.pop();
+    else return true;
+  }
+}
+
+// Captures a wavefront has found, appended to the frame's list in groups (one
+// atomic each).
+constexpr int kPacketCaps = 128;
+
+struct CaptureStage {
+  Capture* buf;   // [kPacketCaps] in LDS
+  int n = 0;      // uniform
+  __device__ void flush(const TraceArgs& a, bool& cap_over) {
+    const int lane = threadIdx.x & (kWave - 1);
+    wave_sync();
+    uint32_t base = 0;
+    if (lane == 0 && n) base = atomicAdd(&a.counters[kCntCaptures], (uint32_t)n);
+    base = __builtin_amdgcn_readfirstlane(base);
+    for (int i = lane; i < n; i += kWave) {
+      if (base + i < a.cap_capacity) a.caps[base + i] = buf[i];
+      else cap_over = true;
+    }
+    n = 0;
+    wave_sync();
+  }
+  __device__ void add(const TraceArgs& a, bool mine, const Capture& c, bool& cap_over) {
+    const uint64_t m = __ballot(mine);
+    if (!m) return;
+    const int count = __popcll(m);
+    if (n + count > kPacketCaps) flush(a, cap_over);
+    if (mine) buf[n + __popcll(m & ((1ull << (threadIdx.x & (kWave - 1))) - 1ull))] = c;
+    n += count;
+  }
+};
+
+// One packet of at most 64 rays: every bounce of all of them, segment by
+// segment (closest hits: the lexicographic minimum of (t, triangle id) over
+// all triangles with t > t_min outside the face just left; boxes are
+// conservative and a node is skipped only when its entry distance exceeds the
+// best hit, so the result does not depend on the tree), captures, reflections,
+// the per-bounce face log and segment cache.  The rays are the positions
+// [p0, p1) of source and branch vsrc or, with kList, the work list's items
+// [p0, p1), each from its restart segment.
+//
+// Consecutive positions are rays of neighbouring directions, and planar faces
+// keep them together: on the urban scene with 2^20 rays a packet enters 10 to
+// 30 nodes per segment where a single ray enters 8 to 17.  A packet that has
+// lost its coherence goes on lane by lane.
+//
+// Bound by vector issue (box tests, and triangle tests in dense scenes) and by
+// the round trips of a packet's dependent node loads, which four wavefronts per
+// SIMD overlap.  Trace times against one ray per lane (us): urban scene, 2^20
+// rays 531 -> 342; 256 sources of 4096 rays 1006 -> 800; indoor office
+// with transmission, 2^18 rays per branch 1210 -> 722; eight cities of up to
+// 2^20 rays in one launch 3500 (with looser trees) -> 2004;
+// toy scene, 4096 rays in packets of 4 81 -> 40; a list of re-traced rays of
+// the highway scene 1405 -> 904.
+template <bool kList>
+__device__ __forceinline__ void trace_packet(const TraceArgs& a, uint32_t vsrc, uint32_t p0, uint32_t p1, int n4,
+                                             CaptureStage& stage, ThreadStack& stack, ItemCounts& ic) {
+  const int lane = threadIdx.x & (kWave - 1);
+  bool live = p0 + lane < p1, moving = false;
+  const bool mine = live;
+  uint32_t pos = live ? p0 + lane : p0;
+  uint32_t work;
+  if constexpr (kList) {
+    work = a.work_list[pos];
+    vsrc = work / (uint32_t)a.n_rays;
+    pos = work - vsrc * (uint32_t)a.n_rays;
+  } else {
+    work = vsrc * (uint32_t)a.n_rays + pos;
+  }
   // the branch's transmitting interactions; segments up to its last one are
   // those of the branch without it, which records their captures
-  const uint32_t tset = a.branch_set[vsrc - txi * (uint32_t)a.n_branch];
+  const uint32_t txi = a.n_branch > 1 ? vsrc / (uint32_t)a.n_branch : vsrc;
+  const uint32_t tset = a.n_branch > 1 ? a.branch_set[vsrc - txi * (uint32_t)a.n_branch] : 0u;
   const int last_t = tset ? 31 - __builtin_clz(tset) : -1;
-  int k = a.restart ? (int)a.restart[work] : 0;
+  const uint32_t rid = a.log_tri ? vsrc * (uint32_t)a.n_rays + a.ray_order[pos] : 0u;
+  const int k0 = kList ? (int)a.restart[work] : 0;
   Ray r;
-  int excl = -1;
   float L = 0.0f;
-  if (k == 0) {
+  int excl = -1, ended = 0;   // ended: segments of the ray once it has ended
+  if (k0 == 0) {
     r.o = make_float3(a.tx[3 * txi], a.tx[3 * txi + 1], a.tx[3 * txi + 2]);
-    r.d = make_float3(a.dirs[3 * ray], a.dirs[3 * ray + 1], a.dirs[3 * ray + 2]);
+    r.d = make_float3(a.dirs[3 * pos], a.dirs[3 * pos + 1], a.dirs[3 * pos + 2]);
   } else {
-    const float4 so = a.seg_o[(size_t)k * a.n_work + work];
-    const float4 sd = a.seg_d[(size_t)k * a.n_work + work];
+    const float4 so = a.seg_o[(size_t)k0 * a.n_work + work];
+    const float4 sd = a.seg_d[(size_t)k0 * a.n_work + work];
     r.o = make_float3(so.x, so.y, so.z);
     r.d = make_float3(sd.x, sd.y, sd.z);
     L = sd.w;
-    excl = a.face_log[(size_t)(k - 1) * a.n_work + work];
+    excl = a.face_log[(size_t)(k0 - 1) * a.n_work + work];
   }
   setup_ray(r);
-  uint32_t state = 0;
-  for (; k <= a.K; ++k) {
-    Hit h = closest_hit(r, a.nodes4, top, n_top, n4, a.tri4, excl, stack, overflow, node_count, tri_count);
-    ++seg_count;
-    const bool hit = h.tri >= 0;
-    const float tend = hit ? h.t : INFINITY;
-    a.face_log[(size_t)k * a.n_work + work] = hit ? h.face : -1;
-    if (hit && a.face_object[h.face] >= 0) state |= 0x80u;
-    if (a.seg_o) {
-      a.seg_o[(size_t)k * a.n_work + work] = make_float4(r.o.x, r.o.y, r.o.z, tend);
-      a.seg_d[(size_t)k * a.n_work + work] = make_float4(r.d.x, r.d.y, r.d.z, L);
+  bool together = true;   // the rays walk the tree as a packet
+  for (int s = 0; s <= a.K; ++s) {
+    const int k = k0 + s;   // the segment (of a live ray at most K)
+    const int n_live = __popcll(__ballot(live));
+    if (n_live == 0) break;
+    Hit h{live ? FLT_MAX : -1.0f, -1, -1, -1};
+    uint32_t entered = 0, lanes = 0;
+    const MaskAxes ax = mask_axes(r);
+    if (n4 > 0 && together) {
+      together = packet_walk(
+          a.nodes4, r, n_live, a.stack_thread, ic.overflow, entered, lanes, [&]() { return fminf(h.t, kFarthest); },
+          [&](int slot, int, bool in) {
+            const Leaf l = *(const Leaf*)((const UniformLeaf*)a.tri4 + slot);
+            const int face = __float_as_int(l.v1.w), tri = __float_as_int(l.v0.w);
+            // (the test runs for every lane: a branch on the face would load it by itself first)
+            const float t = watertight(r, ax, l.v0, l.v1, l.v2);
+            const bool test = in && face != excl;
+            ic.tri += test ? 1u : 0u;
+            if (test && t > kTMin && (t < h.t || (t == h.t && tri < h.tri))) h = Hit{t, tri, slot, face};
+          });
+      if (lane == 0) ic.node += entered;   // a packet's nodes count once
+      if (!together && live) lane_walk(a, r, n4, excl, stack, h, ic);
+      together = together && !incoherent(entered, lanes, n_live);
+    } else if (n4 > 0 && live) {
+      lane_walk(a, r, n4, excl, stack, h, ic);
     }
+    const bool hit = live && h.tri >= 0;
+    const float tend = hit ? h.t : INFINITY;
     const float dd = dot_dd(r);
     const float L_hit = __fmaf_rn(h.t, __fsqrt_rn(dd), L);
-    if (a.log_tri) {
-      const size_t li = (size_t)rid * (a.K + 1) + k;
-      a.log_tri[li] = h.tri;
-      a.log_t[li] = hit ? h.t : INFINITY;
-      a.log_len[li] = hit ? L_hit : INFINITY;
+    Leaf tri{};
+    if (hit) tri = a.tri4[h.leaf];   // for the reflection
+    if (live) {
+      ++ic.seg;
+      a.face_log[(size_t)k * a.n_work + work] = hit ? h.face : -1;
+      if (a.seg_o) {
+        a.seg_o[(size_t)k * a.n_work + work] = make_float4(r.o.x, r.o.y, r.o.z, tend);
+        a.seg_d[(size_t)k * a.n_work + work] = make_float4(r.d.x, r.d.y, r.d.z, L);
+      }
+      if (a.log_tri) {
+        const size_t li = (size_t)rid * (a.K + 1) + k;
+        a.log_tri[li] = h.tri;
+        a.log_t[li] = tend;
+        a.log_len[li] = hit ? L_hit : INFINITY;
+      }
     }
-    if (k > last_t) capture_segment(a, r, hit, h.t, tend, dd, work, txi, k, stack, overflow, cap_over);
-    if (!hit || k == a.K) { ++k; break; }
-    if ((tset >> k) & 1u) {
-      // transmission: straight on through a penetrable face
-      if (!a.face_pen[h.face]) { ++k; break; }
-      L = L_hit;
-      transmit_ray(r, h.t);
-    } else {
-      // specular reflection off the hit triangle's plane, unless the branch
-      // has reflected max_refl times
-      if (k - __popc(tset & ((1u << k) - 1u)) == a.max_refl) { ++k; break; }
-      L = L_hit;
-      reflect_ray(r, h.t, a.tri4[h.leaf].v0, a.tri4[h.leaf].v1, a.tri4[h.leaf].v2);
+    // captures: the packet walks the capture spheres' tree
+    const bool want = live && a.capture && k > last_t && in_rx_band(a, r, hit, h.t);
+    if (!together) {
+      if (want) capture_segment(a, r, hit, h.t, tend, dd, work, txi, k, stack, ic.overflow, ic.cap_over);
+    } else if (__ballot(want)) {
+      const float limit = want ? fminf(tend, kFarthest) : -1.0f;
+      uint32_t rx_entered, rx_lanes;
+      packet_walk(
+          a.rx_nodes, r, 0, a.stack_thread, ic.overflow, rx_entered, rx_lanes, [&]() { return limit; },
+          [&](int, int child, bool in) {
+            if (child == kEmpty) return;
+            const int c = ~child;
+            const UniformFloat* x = (const UniformFloat*)a.rx + 3 * c;
+            const bool got = in && captured(r, tend, dd, x[0], x[1], x[2], a.r2);
+            stage.add(a, got, Capture{work, ((txi * (uint32_t)a.n_rx + (uint32_t)c) << 4) | (uint32_t)k}, ic.cap_over);
+          });
     }
+    // the next segment: straight on through a penetrable face, or specular off
+    // the hit triangle's plane (unless the branch has reflected max_refl
+    // times), or the ray's end
+    if (!live) continue;
+    if (hit && __float_as_int(tri.v2.w)) moving = true;
+    bool more = hit && k < a.K;
+    const bool through = (tset >> k) & 1u;
+    if (more) more = through ? a.face_pen[h.face] != 0 : k - __popc(tset & ((1u << k) - 1u)) != a.max_refl;
+    if (!more) {
+      live = false;
+      ended = k + 1;
+      continue;
+    }
+    L = L_hit;
     excl = h.face;
+    if (through) transmit_ray(r, h.t);
+    else reflect_ray(r, h.t, tri.v0, tri.v1, tri.v2);
   }
-  // mark the remaining bounces as not reached
-  for (int j = k; j <= a.K; ++j) {
+  if (!mine) return;
+  for (int j = ended; j <= a.K; ++j) {   // not reached
     a.face_log[(size_t)j * a.n_work + work] = -2;
     if (a.log_tri) {
       const size_t li = (size_t)rid * (a.K + 1) + j;
@@ -521,11 +752,11 @@ __device__ void trace_item(const TraceArgs& a, uint32_t wi, const Node4* top, in
       a.log_len[li] = INFINITY;
     }
   }
-  a.ray_state[work] = (uint8_t)(state | (uint32_t)k);
+  a.ray_state[work] = (uint8_t)((moving ? 0x80u : 0u) | (uint32_t)ended);
 }
 
-// Wavefront-wide sums of a block's item counts, added to the frame counters
-// (one atomic per wavefront), and its error flags.
+// Sums of a wavefront's item counts added to the frame counters with atomics
+// (the batched trace, whose wavefronts change scenes), and its error flags.
 __device__ void flush_counts(const TraceArgs& a, ItemCounts& ic) {
   uint32_t seg_count = ic.seg, node_count = ic.node, tri_count = ic.tri;
   for (int off = 32; off > 0; off >>= 1) {
@@ -543,32 +774,51 @@ __device__ void flush_counts(const TraceArgs& a, ItemCounts& ic) {
   ic = ItemCounts{};
 }
 
-// Persistent trace kernel: each wavefront takes 64 consecutive work items from
-// a global queue and traces them through all bounces.  In work-list mode a ray
-// restarts at its first invalidated segment from the cached segment state.
-__global__ __launch_bounds__(kTraceBlock) void k_trace(TraceArgs a) {
-  __shared__ int stack_mem[kStackLds * kTraceBlock];
-  __shared__ Node4 top[kTopNodes];
-  ThreadStack stack{stack_mem + threadIdx.x, a.stack_spill + blockIdx.x * (size_t)kTraceBlock + threadIdx.x,
-                    (size_t)gridDim.x * kTraceBlock, a.stack_thread};
-  const int n4 = a.n4_dev ? (int)*a.n4_dev : 0;
-  const int n_top = min(kTopNodes, n4);
-  for (int i = threadIdx.x; i < n_top; i += blockDim.x) top[i] = a.nodes4[i];
+// Sums of a block's item counts, stored for the reduction kernel to add up
+// (one address takes about 90 atomics per microsecond from the whole chip: a
+// few thousand wavefronts adding their counts would queue for tens of
+// microseconds), and its error flags.
+__device__ void store_counts(const TraceArgs& a, const ItemCounts& ic) {
+  __shared__ uint32_t part[3][kPacketBlock / kWave];
+  uint32_t v[3] = {ic.seg, ic.node, ic.tri};
+  for (int off = 32; off > 0; off >>= 1)
+    for (int q = 0; q < 3; ++q) v[q] += __shfl_xor(v[q], off);
+  const int wave = threadIdx.x / kWave, n = blockDim.x / kWave;
+  if ((threadIdx.x & (kWave - 1)) == 0)
+    for (int q = 0; q < 3; ++q) part[q][wave] = v[q];
   __syncthreads();
-  const int lane = threadIdx.x & (kWave - 1);
-  const uint32_t n_work = a.work_list ? a.counters[kCntList] : (uint32_t)a.n_work;
-  if (a.work_list && blockIdx.x == 0 && threadIdx.x == 0) a.counters[kCntWork] = n_work;
-  ItemCounts ic;
-  while (true) {
-    uint32_t base = 0;
-    if (lane == 0) base = atomicAdd(&a.counters[kCntQueue], (uint32_t)kWave);
-    base = __shfl(base, 0);
-    if (base >= n_work) break;
-    const uint32_t wi = base + lane;
-    if (wi < n_work) trace_item(a, wi, top, n_top, n4, stack, ic);
+  if (threadIdx.x < 3) {
+    uint32_t s = 0;
+    for (int w = 0; w < n; ++w) s += part[threadIdx.x][w];
+    a.count_part[3 * blockIdx.x + threadIdx.x] = s;
   }
-  keep_previous_captures(a, ic.cap_over, blockIdx.x);
-  flush_counts(a, ic);
+  if (ic.overflow) atomicOr(a.err, DCEM_ERR_STACK);
+  if (ic.cap_over) atomicOr(a.err, DCEM_ERR_CAPTURES);
+}
+
+// Persistent trace of all rays in packets or, with kList, of the listed rays
+// from their first invalidated segments.
+template <bool kList>
+__global__ __launch_bounds__(kPacketBlock, kPacketPerSimd) void k_trace_packet(TraceArgs a) {
+  __shared__ Capture cap_mem[kPacketBlock / kWave][kPacketCaps];
+  __shared__ int stack_mem[kPacketStack * kPacketBlock];
+  ThreadStack stack{stack_mem + threadIdx.x, a.stack_spill + blockIdx.x * (size_t)kPacketBlock + threadIdx.x,
+                    (size_t)gridDim.x * kPacketBlock, a.stack_thread, kPacketStack, kPacketBlock};
+  const int n4 = a.n4_dev ? (int)*a.n4_dev : 0;
+  CaptureStage stage{cap_mem[threadIdx.x / kWave]};
+  ItemCounts ic;
+  const uint32_t n_pos = kList ? a.counters[kCntList] : (uint32_t)a.n_rays;
+  if (kList && blockIdx.x == 0 && threadIdx.x == 0) a.counters[kCntWork] = n_pos;
+  const uint32_t per_src = (n_pos + a.packet - 1) / a.packet;   // chunks
+  ChunkQueues src(a.queues, kList ? per_src : per_src * (uint32_t)(a.n_src * a.n_branch));
+  uint32_t i;
+  while (src.chunk(i)) {
+    const uint32_t vsrc = kList ? 0u : i / per_src, p0 = (i - vsrc * per_src) * a.packet;
+    trace_packet<kList>(a, vsrc, p0, min(p0 + a.packet, n_pos), n4, stage, stack, ic);
+  }
+  stage.flush(a, ic.cap_over);
+  if (kList) keep_previous_captures(a, ic.cap_over, blockIdx.x);
+  store_counts(a, ic);
 }
 
 // Coherent frames whose receivers moved: the captures of every kept segment
@@ -580,7 +830,7 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace(TraceArgs a) {
 __global__ __launch_bounds__(kTraceBlock) void k_recapture(TraceArgs a) {
   __shared__ int stack_mem[kStackLds * kTraceBlock];
   ThreadStack stack{stack_mem + threadIdx.x, a.stack_spill + blockIdx.x * (size_t)kTraceBlock + threadIdx.x,
-                    (size_t)gridDim.x * kTraceBlock, a.stack_thread};
+                    (size_t)gridDim.x * kTraceBlock, a.stack_thread, kStackLds, kTraceBlock};
   bool overflow = false, cap_over = false;
   const uint32_t n_work = (uint32_t)a.n_work;
   for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < n_work; w += gridDim.x * blockDim.x) {
@@ -609,16 +859,16 @@ __global__ __launch_bounds__(kTraceBlock) void k_recapture(TraceArgs a) {
 // scene j's frame (all rays, no work list); its items are cut into chunks of
 // `chunk` consecutive work items, chunk_start[j] the first chunk of scene j in
 // one queue over all scenes (chunk_start[n] the total).  A wavefront takes the
-// next chunk, finds its scene and traces the chunk's items, 64 at a time;
-// counts and errors go to that scene's frame.  The per-thread stack keeps its
-// first S entries in LDS.  No top-level node cache: consecutive chunks may
-// belong to different scenes.
+// next chunk, finds its scene and traces the chunk's items in packets; counts
+// and errors go to that scene's frame.  A lane's stack keeps its first S entries
+// in LDS.
 template <int S>
-__global__ __launch_bounds__(kTraceBlock) void k_trace_batch(const TraceArgs* __restrict__ args,
+__global__ __launch_bounds__(kTraceBlock, kPacketPerSimd) void k_trace_batch(const TraceArgs* __restrict__ args,
                                                              const uint32_t* __restrict__ chunk_start, int n_scene,
                                                              uint32_t chunk, uint32_t* __restrict__ queue,
                                                              int* __restrict__ spill) {
   __shared__ int stack_mem[S * kTraceBlock];
+  __shared__ Capture cap_mem[kTraceBlock / kWave][kPacketCaps];
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t total = chunk_start[n_scene];
   while (true) {
@@ -633,14 +883,19 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_batch(const TraceArgs* __
     }
     const TraceArgs a = args[lo];
     ThreadStack stack{stack_mem + threadIdx.x, spill + blockIdx.x * (size_t)kTraceBlock + threadIdx.x,
-                      (size_t)gridDim.x * kTraceBlock, a.stack_thread};
-    stack.lds_entries = S;
+                      (size_t)gridDim.x * kTraceBlock, a.stack_thread, S, kTraceBlock};
     const int n4 = a.n4_dev ? (int)*a.n4_dev : 0;
     const uint32_t base = (g - chunk_start[lo]) * chunk;
     const uint32_t end = min(base + chunk, (uint32_t)a.n_work);
     ItemCounts ic;
-    for (uint32_t b = base; b < end; b += kWave)
-      if (b + lane < end) trace_item(a, b + lane, nullptr, 0, n4, stack, ic);
+    CaptureStage stage{cap_mem[threadIdx.x / kWave]};
+    for (uint32_t w = base; w < end;) {
+      const uint32_t vsrc = w / (uint32_t)a.n_rays, p0 = w - vsrc * (uint32_t)a.n_rays;
+      const uint32_t p1 = min(min(p0 + (uint32_t)kWave, p0 + (end - w)), (uint32_t)a.n_rays);
+      trace_packet<false>(a, vsrc, p0, p1, n4, stage, stack, ic);
+      w += p1 - p0;
+    }
+    stage.flush(a, ic.cap_over);
     flush_counts(a, ic);
   }
 }
@@ -664,8 +919,6 @@ __global__ __launch_bounds__(kTraceBlock) void k_trace_batch(const TraceArgs* __
 constexpr int kRayLanes = kGroup;
 constexpr int kGroups = kWave / kRayLanes;  // rays per wavefront
 constexpr int kRayStack = kRayLanes == 64 ? 256 : kGroupStack;   // stack entries per ray
-constexpr int kWaves = 4;                   // wavefronts per block
-constexpr int kWaveBlock = kWaves * kWave;
 constexpr int kWaveRx = 512;                // receivers cached in LDS (more are read from memory)
 constexpr int kCapStage = 256;              // new captures a block stages in LDS
 constexpr int64_t kWaveTraceMax = 1 << 16;  // longest list traced by groups
@@ -721,12 +974,6 @@ __device__ inline uint64_t group_min_u64(uint64_t v) {
     v = o < v ? o : v;
   }
   return v;
-}
-
-__device__ inline MaskAxes mask_axes(const Ray& r) {
-  auto m = [](int k, int j) { return k == j ? 0xffffffffu : 0u; };
-  return MaskAxes{m(r.kx, 0), m(r.kx, 1), m(r.kx, 2), m(r.ky, 0), m(r.ky, 1),
-                  m(r.ky, 2), m(r.kz, 0), m(r.kz, 1), m(r.kz, 2)};
 }
 
 
@@ -800,14 +1047,14 @@ __global__ __launch_bounds__(kWaveBlock) void k_trace_wave(TraceArgs a) {
     if (!busy) return;
     work = first ? work0 : a.work_list[item];
     txi = (uint32_t)(work / (uint64_t)a.n_rays);
-    const uint32_t ray = a.ray_order[work - (uint64_t)txi * a.n_rays];
-    rid = txi * (uint32_t)a.n_rays + ray;
+    const uint32_t pos = work - txi * (uint32_t)a.n_rays;
+    rid = a.log_tri ? txi * (uint32_t)a.n_rays + a.ray_order[pos] : 0u;
     k = (int)a.restart[work];
     excl = -1;
     L = 0.0f;
     if (k == 0) {
       r.o = make_float3(a.tx[3 * txi], a.tx[3 * txi + 1], a.tx[3 * txi + 2]);
-      r.d = make_float3(a.dirs[3 * ray], a.dirs[3 * ray + 1], a.dirs[3 * ray + 2]);
+      r.d = make_float3(a.dirs[3 * pos], a.dirs[3 * pos + 1], a.dirs[3 * pos + 2]);
     } else {
       const float4 so = a.seg_o[(size_t)k * a.n_work + work];
       const float4 sd = a.seg_d[(size_t)k * a.n_work + work];
@@ -870,7 +1117,7 @@ __global__ __launch_bounds__(kWaveBlock) void k_trace_wave(TraceArgs a) {
     if (leaf) {
       const int face = __float_as_int(q1.w);
       if (face != excl) {
-        const float t = watertight_axes(r, ax, q0, q1, q2);
+        const float t = watertight(r, ax, q0, q1, q2);
         const int tri = __float_as_int(q0.w);
         if (t > kTMin && hit_less(t, tri, h.t, h.tri)) {
           improved = true;
@@ -1034,18 +1281,13 @@ __global__ __launch_bounds__(kWaveBlock) void k_trace_wave(TraceArgs a) {
     if (slot < a.cap_capacity) a.caps[slot] = scap[j];
     else cap_over = true;
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    seg_count += __shfl_xor(seg_count, off);
-    node_count += __shfl_xor(node_count, off);
-    tri_count += __shfl_xor(tri_count, off);
-  }
-  if (lane == 0) {
-    atomicAdd(&a.counters[kCntSegments], seg_count);
-    atomicAdd(reinterpret_cast<unsigned long long*>(&a.counters[kCntNodes]), (unsigned long long)node_count);
-    atomicAdd(reinterpret_cast<unsigned long long*>(&a.counters[kCntTris]), (unsigned long long)tri_count);
-  }
-  if (overflow) atomicOr(a.err, DCEM_ERR_STACK);
-  if (cap_over) atomicOr(a.err, DCEM_ERR_CAPTURES);
+  ItemCounts ic;
+  ic.seg = seg_count;
+  ic.node = node_count;
+  ic.tri = tri_count;
+  ic.overflow = overflow;
+  ic.cap_over = cap_over;
+  store_counts(a, ic);
 }
 
 // Start of a frame's lists: the counters reset (the revalidation's list
@@ -1062,10 +1304,12 @@ struct FrameBegin {
   // fallback flag) makes the launch do nothing: that frame's candidates must
   // be redone on the tree it was traced with before the next frame begins
   const uint32_t* skip;
+  uint32_t* queues;   // the trace's chunk queues, emptied
 };
 
 __device__ inline void frame_begin_part(const FrameBegin& f, int t, int nt, bool keep_list) {
   if (t < kCntSlots && !(keep_list && t == kCntList)) f.counters[t] = t == kCntCaptures ? f.n_los : 0;
+  if (t < kXcds) f.queues[t * kQueueStride] = 0;
   for (int p = t; p < f.n_los; p += nt) {
     if (p < f.cap_capacity) {
       Capture c;
@@ -1387,6 +1631,17 @@ __global__ void k_dir_keys(const float* __restrict__ dirs, int64_t n, uint32_t* 
   key[i] = (spread16(qu) << 1) | spread16(qv);
 }
 
+// Directions in traversal order.
+__global__ void k_dirs_by_pos(const float* __restrict__ dirs, const uint32_t* __restrict__ order, int64_t n,
+                              float* __restrict__ out) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const float* d = dirs + 3 * (size_t)order[i];
+  out[3 * i] = d[0];
+  out[3 * i + 1] = d[1];
+  out[3 * i + 2] = d[2];
+}
+
 int cu_count(dcem_ctx* c) {
   if (c->n_cus == 0) {
     hipDeviceProp_t prop;
@@ -1397,7 +1652,7 @@ int cu_count(dcem_ctx* c) {
 }
 
 int trace_grid(dcem_ctx* c) {
-  return cu_count(c) * 8;   // 16 KB of LDS stack and 2.7 KB of top nodes per block: eight blocks per CU
+  return cu_count(c) * 8;   // 16 KB of LDS stack per block: eight blocks per CU
 }
 
 }  // namespace
@@ -1419,13 +1674,13 @@ TraceArgs trace_args(dcem_ctx* c, bool all_rays, bool keep_cache, uint32_t n_pre
   a.nodes4 = ptr<Node4>(c->nodes4);
   a.tri4 = ptr<Leaf>(c->tri4);
   a.n4_dev = c->nt > 0 ? ptr<uint32_t>(c->tree_info) : nullptr;
-  a.dirs = ptr<float>(c->dirs);
+  a.dirs = ptr<float>(c->dirs_by_pos);
   a.ray_order = ptr<uint32_t>(c->ray_order);
   a.tx = ptr<float>(c->src_pos);
   a.rx = ptr<float>(c->tgt_pos);
   a.n_rx = c->n_tgt;
   a.capture = c->visited ? 0 : 1;
-  a.rx_nodes = ptr<Node>(c->rx_nodes);
+  a.rx_nodes = ptr<Node4>(c->rx_nodes);
   a.n_rx_nodes = c->n_rx_nodes;
   a.restart = all_rays ? nullptr : ptr<uint8_t>(c->invalid_flag);
   a.r2 = c->cfg.rx_radius * c->cfg.rx_radius;
@@ -1444,6 +1699,8 @@ TraceArgs trace_args(dcem_ctx* c, bool all_rays, bool keep_cache, uint32_t n_pre
   a.rx_col_scale = c->rx_col_scale;
   a.n_rays = c->n_rays;
   a.n_work = (int)n_work;
+  a.n_src = c->n_src;
+  a.packet = kWave;
   a.work_list = all_rays ? nullptr : ptr<uint32_t>(c->work_list);
   a.K = c->K;
   a.max_refl = c->max_refl;
@@ -1452,6 +1709,7 @@ TraceArgs trace_args(dcem_ctx* c, bool all_rays, bool keep_cache, uint32_t n_pre
   a.face_pen = ptr<uint8_t>(c->face_pen);
   a.face_object = ptr<int32_t>(c->face_object);
   a.counters = c->cnt_dev;
+  a.queues = ptr<uint32_t>(c->queues);
   a.face_log = ptr<int32_t>(c->face_log);
   a.ray_state = ptr<uint8_t>(c->ray_state);
   a.seg_o = keep_cache ? ptr<float4>(c->seg_o) : nullptr;
@@ -1462,6 +1720,7 @@ TraceArgs trace_args(dcem_ctx* c, bool all_rays, bool keep_cache, uint32_t n_pre
   a.caps = ptr<Capture>(c->caps[c->cur_caps]);
   a.cap_capacity = c->cap_capacity;
   a.err = c->err_dev;
+  a.count_part = ptr<uint32_t>(c->count_part);
   a.prev_caps = ptr<Capture>(c->caps[c->cur_caps ^ 1]);
   a.n_prev = all_rays ? 0u : n_prev_caps;
   a.stack_spill = nullptr;
@@ -1478,17 +1737,29 @@ int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, 
     // short re-trace list: one wavefront per ray
     const int64_t want = (expected + expected / 4 + kWaves * kGroups - 1) / (kWaves * kGroups) + 1;
     const int grid = (int)std::max<int64_t>(16, std::min<int64_t>((int64_t)cu_count(c) * 8, want));
+    c->count_blocks = grid;
     hipLaunchKernelGGL(k_trace_wave, dim3(grid), dim3(kWaveBlock), 0, c->stream, a);
     return 1;
   }
-  const int64_t want = (expected + expected / 4 + kTraceBlock - 1) / kTraceBlock;
-  const int grid = (int)std::max<int64_t>(16, std::min<int64_t>(trace_grid(c), want));
+  // packets of 64 rays, or of fewer while that leaves the chip idle: 4096 rays
+  // take 75 us in packets of 64 and 40 us in packets of 4, 65536 rays 129 us at
+  // 8, 16 or 32 wavefronts per compute unit (a list may turn out a quarter
+  // longer than the last frame's)
+  const int64_t n = all_rays ? c->n_rays : expected + expected / 4 + 1;
+  const int64_t lists = all_rays ? (int64_t)c->n_src * c->n_branch : 1;
+  const int64_t cu = cu_count(c);
+  a.packet = kWave;
+  while (a.packet > kMinPacket && lists * ((n + a.packet - 1) / a.packet) < cu * kPacketWaves) a.packet /= 2;
+  const int64_t want = (lists * ((n + a.packet - 1) / a.packet) * kWave + kPacketBlock - 1) / kPacketBlock;
+  const int grid = (int)std::max<int64_t>(16, std::min<int64_t>(cu * kPacketPerSimd, want));
   if (prepare_trace(c) != hipSuccess) {   // sized already by the frame's setup
     (void)hipGetLastError();
     return -1;
   }
   a.stack_spill = ptr<int>(c->stack_spill);
-  hipLaunchKernelGGL(k_trace, dim3(grid), dim3(kTraceBlock), 0, c->stream, a);
+  c->count_blocks = grid;
+  if (all_rays) hipLaunchKernelGGL(k_trace_packet<false>, dim3(grid), dim3(kPacketBlock), 0, c->stream, a);
+  else hipLaunchKernelGGL(k_trace_packet<true>, dim3(grid), dim3(kPacketBlock), 0, c->stream, a);
   return 0;
 }
 
@@ -1549,13 +1820,20 @@ void launch_recapture(dcem_ctx* c) {
 }
 
 hipError_t prepare_trace(dcem_ctx* c) {
-  // spill space for the largest grid, so it never changes from frame to frame
-  return ensure(c->stack_spill, sizeof(int) * kStackSpill * kTraceBlock * (size_t)std::max(trace_grid(c), 16));
+  // spill space and counts for the largest grid, so they never change from frame to frame
+  hipError_t e = ensure(c->queues, sizeof(uint32_t) * kXcds * kQueueStride);
+  if (e != hipSuccess) return e;
+  e = ensure(c->count_part, sizeof(uint32_t) * 3 * (size_t)std::max(cu_count(c) * 8, 16));
+  if (e != hipSuccess) return e;
+  const size_t packet =
+      (size_t)(kStackSize - kPacketStack) * kPacketBlock * (size_t)std::max(cu_count(c) * kPacketPerSimd, 16);
+  const size_t recapture = (size_t)kStackSpill * kTraceBlock * (size_t)std::max(trace_grid(c), 16);
+  return ensure(c->stack_spill, sizeof(int) * std::max(packet, recapture));
 }
 
 FrameBegin frame_begin_args(dcem_ctx* c, bool los) {
   return FrameBegin{c->cnt_dev, ptr<Capture>(c->caps[c->cur_caps]), los ? c->n_src * c->n_tgt : 0, c->cap_capacity,
-                    c->err_dev, nullptr};
+                    c->err_dev, nullptr, ptr<uint32_t>(c->queues)};
 }
 
 void launch_frame_begin(dcem_ctx* c, bool los, const uint32_t* skip) {
@@ -1638,6 +1916,9 @@ hipError_t build_ray_order(dcem_ctx* c) {
   const uint32_t n32 = (uint32_t)n;
   if ((e = hipMemcpyAsync(n_dev, &n32, 4, hipMemcpyHostToDevice, c->stream)) != hipSuccess) return e;
   if ((e = radix_sort_perm(c, key, 1, 32, n_dev, n, order, tmp, c->stream)) != hipSuccess) return e;
+  if ((e = ensure(c->dirs_by_pos, sizeof(float) * 3 * (size_t)n)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_dirs_by_pos, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, ptr<float>(c->dirs),
+                     order, n, ptr<float>(c->dirs_by_pos));
   return hipStreamSynchronize(c->stream);
 }
 
