@@ -409,11 +409,13 @@ __global__ __launch_bounds__(kRefitBlock) void k_refit_cross(RefitArgs a, int n_
 // surface-area sums.
 double* sah_parts(dcem_ctx* c) { return reinterpret_cast<double*>(ptr<char>(c->scene_box) + 8 * sizeof(float)); }
 
-// Depth of each binary internal node (steps to the root) as a sort key: nodes
-// at even depth become 4-wide nodes and are ordered by (depth, index), i.e.
-// breadth-first; odd-depth nodes sort to the end.
-__global__ void k_depth_keys(const Node* __restrict__ nodes, int n_internal, uint32_t* __restrict__ key,
-                             uint32_t* __restrict__ n_even) {
+// Depth of each binary internal node (steps to the root) as a sort key of one
+// digit: nodes at even depth become 4-wide nodes and are ordered by (depth,
+// index), i.e. breadth-first (the sort is stable; below depth 508 by index
+// alone); odd-depth nodes sort to the end.
+constexpr uint32_t kOddDepth = 255;
+
+__global__ void k_depth_keys(const Node* __restrict__ nodes, int n_internal, uint32_t* __restrict__ key) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_internal) return;
   int d = 0, p2 = nodes[i].c.z;
@@ -421,20 +423,20 @@ __global__ void k_depth_keys(const Node* __restrict__ nodes, int n_internal, uin
     ++d;
     p2 = nodes[p2 >> 1].c.z;
   }
-  const bool even = (d & 1) == 0;
-  key[i] = even ? ((uint32_t)d << 26) | (uint32_t)i : 0xffffffffu;
-  if (even) atomicAdd(n_even, 1u);
+  key[i] = (d & 1) == 0 ? min((uint32_t)d / 2, kOddDepth - 1) : kOddDepth;
 }
 
-// 4-wide node of each even-depth binary node (-1 for odd depth).
-__global__ void k_map4(const uint32_t* __restrict__ perm, const uint32_t* __restrict__ n4_dev, int n_internal,
-                       int32_t* __restrict__ bvh2_of, int32_t* __restrict__ map4) {
+// 4-wide node of each even-depth binary node (-1 for odd depth), and their
+// number.
+__global__ void k_map4(const uint32_t* __restrict__ perm, const uint32_t* __restrict__ key, int n_internal,
+                       int32_t* __restrict__ bvh2_of, int32_t* __restrict__ map4, uint32_t* __restrict__ n4_dev) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= n_internal) return;
   const int p = (int)perm[q];
-  if (q < (int)*n4_dev) {
+  if (key[p] != kOddDepth) {
     bvh2_of[q] = p;
     map4[p] = q;
+    if (q + 1 == n_internal || key[perm[q + 1]] == kOddDepth) *n4_dev = (uint32_t)q + 1;
   } else {
     map4[p] = -1;
   }
@@ -738,11 +740,11 @@ hipError_t tree_from_keys(dcem_ctx* c, int key_words, int key_bits) {
   uint32_t* dtmp = dperm + ni;
   uint32_t* dn = dtmp + ni;   // item count for the sort
   uint32_t* n4 = ptr<uint32_t>(c->tree_info);   // [0] = 4-wide node count
-  hipLaunchKernelGGL(k_set2, dim3(1), dim3(64), 0, c->stream, n4, 0u, dn, (uint32_t)ni);
-  hipLaunchKernelGGL(k_depth_keys, dim3((ni + 255) / 256), dim3(256), 0, c->stream, ptr<Node>(c->nodes), ni, dkey, n4);
-  if ((e = radix_sort_perm(c, dkey, 1, 32, dn, ni, dperm, dtmp, c->stream)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_map4, dim3((ni + 255) / 256), dim3(256), 0, c->stream, dperm, n4, ni,
-                     ptr<int32_t>(c->bvh2_of4), ptr<int32_t>(c->map4));
+  hipLaunchKernelGGL(k_set2, dim3(1), dim3(64), 0, c->stream, dn, (uint32_t)ni, dn, (uint32_t)ni);
+  hipLaunchKernelGGL(k_depth_keys, dim3((ni + 255) / 256), dim3(256), 0, c->stream, ptr<Node>(c->nodes), ni, dkey);
+  if ((e = radix_sort_perm(c, dkey, 1, 8, dn, ni, dperm, dtmp, c->stream)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_map4, dim3((ni + 255) / 256), dim3(256), 0, c->stream, dperm, dkey, ni,
+                     ptr<int32_t>(c->bvh2_of4), ptr<int32_t>(c->map4), n4);
   launch_collapse(c);
   // slot of every face triangle, for the refinement's face test (face_tris
   // lists every triangle once, grouped by face)

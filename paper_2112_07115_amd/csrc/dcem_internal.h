@@ -358,7 +358,7 @@ hipError_t radix_sort_perm(dcem_ctx* c, const uint32_t* keys, int W, int bits, c
                            int low_bits = 32);
 // The sort's histogram space for up to n_max items (sized before a frame that
 // a graph may capture).
-hipError_t prepare_sort(dcem_ctx* c, int64_t n_max);
+hipError_t prepare_sort(dcem_ctx* c, int bits, int64_t n_max);
 
 // ---- trace (trace.hip)
 void launch_fibonacci(dcem_ctx* c);

@@ -1664,7 +1664,7 @@ hipError_t prepare_sorted_candidates(dcem_ctx* c, int64_t n) {
   if ((e = ensure(c->cand_tmp, n + 16 + sizeof(uint32_t) * (nb + 8))) != hipSuccess) return e;
   if ((e = ensure(c->uniq_idx, sizeof(uint32_t) * (n + 1))) != hipSuccess) return e;
   if ((e = ensure_paths(c, n)) != hipSuccess) return e;
-  return prepare_sort(c, n);
+  return prepare_sort(c, L.bits, n);
 }
 
 namespace {
