@@ -441,7 +441,7 @@ dcem_status check_device_error(dcem_ctx* c) { return sync_frame(c); }
 dcem_status finish_candidates(dcem_ctx* c) {
   HIP_TRY(build_candidates(c, false), "candidates");
   HIP_TRY(ensure_paths(c, c->path_cap), "alloc paths");
-  launch_refine(c);
+  launch_refine(c, c->path_cap);
   launch_reduce(c);
   HIP_TRY(hipGetLastError(), "refine kernels");
   return DCEM_OK;
@@ -1051,7 +1051,8 @@ dcem_status frame_back(dcem_ctx* c, const FramePlan& plan) {
   }
   ev_record(c, 3);
   HIP_TRY(ensure_paths(c, c->path_cap), "alloc paths");
-  launch_refine(c);
+  // a hinted list's candidates: about as many as the last frame's
+  launch_refine(c, plan.hint > 0 ? (int64_t)c->last_cnt[kCntUnique] : c->path_cap);
   ev_record(c, 4);
   launch_reduce(c);
   c->list_clear = true;

@@ -361,6 +361,7 @@ hipError_t radix_sort_perm(dcem_ctx* c, const uint32_t* keys, int W, int bits, c
 hipError_t prepare_sort(dcem_ctx* c, int bits, int64_t n_max);
 
 // ---- trace (trace.hip)
+int cu_count(dcem_ctx* c);   // compute units of the context's device
 void launch_fibonacci(dcem_ctx* c);
 // Trace all rays, or (coherent frame) the listed ones after keeping the
 // previous frame's still-valid captures.  Returns the traversal launched:
@@ -412,7 +413,8 @@ hipError_t prepare_small_candidates(dcem_ctx* c);
 bool small_path_fits(const dcem_ctx* c);
 int64_t small_path_capacity();
 hipError_t ensure_paths(dcem_ctx* c, int64_t n);
-void launch_refine(dcem_ctx* c);
+// expected: candidates, roughly (any number is refined)
+void launch_refine(dcem_ctx* c, int64_t expected);
 void launch_reduce(dcem_ctx* c);
 void launch_power_grad(dcem_ctx* c, uint32_t n_unique, double* g_eps, double* g_sig, double* g_pat);
 

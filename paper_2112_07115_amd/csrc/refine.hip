@@ -446,6 +446,10 @@ __global__ __launch_bounds__(256) void k_unique_info(const uint32_t* __restrict_
 }
 
 
+// Products are fused with sums inside one expression only, so that kernels that
+// share these functions get the same bits from them.
+#pragma clang fp contract(on)
+
 struct D3 {
   double x, y, z;
 };
@@ -579,7 +583,7 @@ struct RefineArgs {
 // Is point p inside one of the triangles k0, k0 + step, ... of face f
 // (inclusive)?  2D edge functions on the plane projection that drops the
 // normal's dominant axis.  (k0 = 0, step = 1: inside the face.)
-__device__ bool in_face(const RefineArgs& a, int f, D3 p, D3 n, int k0 = 0, int step = 1) {
+__device__ __forceinline__ bool in_face(const RefineArgs& a, int f, D3 p, D3 n, int k0 = 0, int step = 1) {
   const double ax = fabs(n.x), ay = fabs(n.y), az = fabs(n.z);
   const int drop = (ax >= ay && ax >= az) ? 0 : (ay >= az ? 1 : 2);
   auto pr = [drop](D3 v, double& u, double& w) {
@@ -607,37 +611,58 @@ __device__ bool in_face(const RefineArgs& a, int f, D3 p, D3 n, int k0 = 0, int 
 // Any triangle (outside faces fa, fb) crossed by the open segment p -> q,
 // keeping t_min away from both ends?  FP64 orientation tests at the leaves;
 // 4-wide tree boxes (FP32, padded) tested in FP64.  Traversed by a group of
-// kCheckLanes lanes, one tree level per step: each lane takes one slot of up
-// to kCheckLanes / 4 popped nodes (a stack entry carries its node's leaf-slot
-// mask, so leaf triangles come straight from the slot array).  The answer does
-// not depend on the order: the first occluder found ends the query, and an
+// kLanes lanes, one tree level per step: each lane takes one slot of up to
+// kLanes / 4 popped nodes (a stack entry carries its node's leaf-slot mask, so
+// leaf triangles come straight from the slot array).  The answer does not
+// depend on the order: the first occluder found ends the query, and an
 // unoccluded segment visits every box it meets, so a wide group takes few
-// steps.
-constexpr int kCheckLanes = kWave;              // lanes per occlusion query
+// steps; a narrow one leaves fewer lanes idle.
 constexpr int kCheckStack = 256;                // stack entries per query
 
-__device__ bool group_occluded(const RefineArgs& a, D3 p, D3 q, int fa, int fb, uint32_t* se, int lane,
-                               uint64_t gmask, bool& fault) {
-  const int n4 = a.n4_dev ? (int)a.n4_dev[0] : 0;
-  if (n4 == 0) return false;
-  const D3 dv = q - p;
-  const double L = len(dv);
-  const double tlo = kTMinD / L, thi = 1.0 - kTMinD / L;
-  if (!(tlo < thi)) return false;
-  const double big = 1e300;
-  const double ix = dv.x != 0 ? 1.0 / dv.x : big, iy = dv.y != 0 ? 1.0 / dv.y : big,
-               iz = dv.z != 0 ? 1.0 / dv.z : big;
-  const int gl = lane & (kCheckLanes - 1), jl = gl >> 2, el = gl & 3;
-  const uint64_t below = (1ull << lane) - 1ull;
-  if (gl == 0) se[0] = a.n4_dev[1] << kNodeBits;
-  int sp = 1;
-  wave_sync();
-  for (int guard = n4 + 2; sp > 0; --guard) {
-    if (guard == 0) {
+template <int kLanes>
+struct Occlusion {
+  const RefineArgs& a;
+  uint32_t* se;        // the group's stack in LDS
+  int lane, gl;        // lane of the wavefront and of the group
+  uint64_t gmask;      // the group's lanes
+  D3 p, q;
+  double ix, iy, iz, tlo, thi;
+  int fa, fb, sp = 0, guard = 0;   // sp: stack entries, 0 once no box is left
+  __device__ Occlusion(const RefineArgs& a_, uint32_t* stack, int lane_, uint64_t mask)
+      : a(a_), se(stack), lane(lane_), gl(lane_ & (kLanes - 1)), gmask(mask) {}
+
+  __device__ __forceinline__ void begin(D3 p_, D3 q_, int fa_, int fb_) {
+    p = p_;
+    q = q_;
+    fa = fa_;
+    fb = fb_;
+    sp = 0;
+    const int n4 = a.n4_dev ? (int)a.n4_dev[0] : 0;
+    if (n4 == 0) return;
+    const D3 dv = q - p;
+    const double L = len(dv);
+    tlo = kTMinD / L;
+    thi = 1.0 - kTMinD / L;
+    if (!(tlo < thi)) return;
+    const double big = 1e300;
+    ix = dv.x != 0 ? 1.0 / dv.x : big;
+    iy = dv.y != 0 ? 1.0 / dv.y : big;
+    iz = dv.z != 0 ? 1.0 / dv.z : big;
+    if (gl == 0) se[0] = a.n4_dev[1] << kNodeBits;
+    sp = 1;
+    guard = n4 + 2;
+    wave_sync();
+  }
+
+  // One step; true when an occluder was found.
+  __device__ __forceinline__ bool step(bool& fault) {
+    const int jl = gl >> 2, el = gl & 3;
+    if (guard-- == 0) {
       fault = true;
+      sp = 0;
       return false;
     }
-    const int n_pop = min(kCheckLanes / 4, sp);
+    const int n_pop = min(kLanes / 4, sp);
     const bool act = jl < n_pop;
     const uint32_t ent = act ? se[sp - 1 - jl] : 0u;
     wave_sync();
@@ -675,16 +700,19 @@ __device__ bool group_occluded(const RefineArgs& a, D3 p, D3 q, int fa, int fb, 
       const double tf = fmin(fmin(fmax(ax, bx), fmax(ay, by)), fmin(fmax(az, bz), 1.0));
       if (tn <= tf * (1.0 + 1e-12)) push = (uint32_t)__float_as_int(q0.w) | (__float_as_uint(q1.w) << kNodeBits);
     }
-    if (__ballot(hit) & gmask) return true;
+    if (__ballot(hit) & gmask) {
+      sp = 0;
+      return true;
+    }
     const uint64_t want = __ballot(push != kNoEntry) & gmask;
-    const int pos = sp + __popcll(want & below);
+    const int pos = sp + __popcll(want & ((1ull << lane) - 1ull));
     if (push != kNoEntry && pos < kCheckStack) se[pos] = push;
     if (sp + __popcll(want) > kCheckStack) fault = true;
     sp = min(sp + __popcll(want), kCheckStack);
     wave_sync();
+    return false;
   }
-  return false;
-}
+};
 
 // The image of point im in plane pl (unit normal xyz, offset w), with
 // contraction off: the refinement and the visited-series expansion both
@@ -736,117 +764,203 @@ __device__ inline bool through_opaque(const RefineArgs& a, const int* faces, int
   return false;
 }
 
-// Refinement of one unique candidate u by one block of four wavefronts (one
-// per SIMD, so four blocks share a compute unit; blocks of more wavefronts
-// place two on the same SIMD and only two of them fit).
-//  1. Geometry (wavefront 0: lane j loads face j's plane, lane 0 walks):
-//     decode the key, image sources through the face planes and reflection
-//     points walked back from the receiver, each strictly inside its segment
-//     (Sec. III step 3).
-//  2. One validation task per sub-segment j = 0..order: the sub-segment must
-//     be unoccluded (every triangle outside its end faces), and for j >= 1
-//     reflection point j must lie in its face, the face's triangles spread
-//     over the lanes (Sec. III step 4).
-//  3. The field task (lane f for frequency f): length, delay, directions and
-//     the field: theta-hat of the departure direction carried through each
-//     reflection by the Fresnel coefficients, times sqrt(Pt) lambda /
-//     (4 pi d), the specific attenuation and the phase e^{-j k0 d} (Eq. (3)
-//     with n = 2, Sec. III step 6).
-// The tasks are drawn in a fixed order from an LDS counter (wavefront w
+// A candidate being refined, in LDS.
+struct RefineCand {
+  double P[(kMaxK + 2) * 3];   // transmitter, reflection points, receiver
+  D3 img[kMaxK + 1];           // images of the transmitter
+  double4 pl[kMaxK];           // planes of the faces
+  double d;                    // path length
+  int faces[kMaxK];            // face ids (transmission flag cleared)
+  int seg[kMaxK + 1];          // the sub-segments, longest first
+  int order, ok;
+  uint32_t tmask;              // bit j - 1: interaction j transmits
+  __device__ D3 pt(int j) const { return D3{P[3 * j], P[3 * j + 1], P[3 * j + 2]}; }
+};
+
+// Image-method geometry of candidate u by one lane: image sources through the
+// face planes and reflection points walked back from the receiver, each
+// strictly inside its segment (Sec. III step 3).
+__device__ __forceinline__ void refine_geometry(const RefineArgs& a, uint32_t u, int pair, int order, uint32_t tm, RefineCand& s) {
+  const int tx = pair / a.n_rx, rx = pair - tx * a.n_rx;
+  const D3 T = fvec(a.tx, tx), R = fvec(a.rx, rx);
+  s.tmask = tm;
+  s.P[0] = T.x; s.P[1] = T.y; s.P[2] = T.z;
+  s.P[3 * (order + 1)] = R.x; s.P[3 * (order + 1) + 1] = R.y; s.P[3 * (order + 1) + 2] = R.z;
+  // the images, forward once (reflect_image), kept in LDS for the walk
+  D3 im = T;
+  s.img[0] = im;
+  for (int j = 1; j <= order; ++j) {
+    if (!((tm >> (j - 1)) & 1u)) im = reflect_image(im, s.pl[j - 1]);
+    s.img[j] = im;
+  }
+  bool ok = image_walk(
+      R, order, [&](int j) { return s.img[j]; }, [&](int j) { return s.pl[j]; },
+      [&](int j, D3 q) {
+        s.P[3 * j] = q.x; s.P[3 * j + 1] = q.y; s.P[3 * j + 2] = q.z;
+        return true;
+      },
+      s.d);
+  ok = ok && !through_opaque(a, s.faces, order, tm);
+  double* P = a.pts + (size_t)u * (a.K + 2) * 3;
+  for (int j = 0; j < 3 * (order + 2); ++j) P[j] = s.P[j];
+  a.length[u] = s.d;
+  s.order = order;
+  s.ok = ok ? 1 : 0;
+  // the sub-segments, longest first: an occlusion query's cost grows with the
+  // length it crosses
+  double seg_len[kMaxK + 1];
+  for (int j = 0; j <= order; ++j) {
+    const D3 e = s.pt(j + 1) - s.pt(j);
+    const double l2 = dot(e, e);
+    int i = j;
+    for (; i > 0 && seg_len[i - 1] < l2; --i) {
+      seg_len[i] = seg_len[i - 1];
+      s.seg[i] = s.seg[i - 1];
+    }
+    seg_len[i] = l2;
+    s.seg[i] = j;
+  }
+}
+
+// The field of candidate u, lane gl of n taking frequencies gl, gl + n, ...:
+// theta-hat of the departure direction carried through each reflection by the
+// Fresnel coefficients, times sqrt(Pt) lambda / (4 pi d), the specific
+// attenuation and the phase e^{-j k0 d} (Eq. (3) with n = 2, Sec. III step 6).
+__device__ __forceinline__ void refine_field(const RefineArgs& a, uint32_t u, const RefineCand& s, int gl, int n) {
+  const int order = s.order;
+  const double d = s.d;
+  const D3 aod = normed(s.pt(1) - s.pt(0));
+  const double rho = sqrt(aod.x * aod.x + aod.y * aod.y);
+  const D3 e0 = rho > 0 ? D3{aod.z * aod.x / rho, aod.z * aod.y / rho, -rho} : D3{aod.z, 0.0, 0.0};
+  const double gain = pattern_gain(a.pat, aod);
+  for (int fi = gl; fi < a.n_freqs; fi += n) {
+    const double f = a.freqs[fi];
+    double* out = a.amp + ((size_t)u * a.n_freqs + fi) * 6;
+    Cx E[3] = {{e0.x, 0}, {e0.y, 0}, {e0.z, 0}};
+    for (int j = 1; j <= order; ++j) {
+      if ((s.tmask >> (j - 1)) & 1u) {
+        // transmission: the penetration loss of the face's material
+        // (Table II), polarisation and direction unchanged
+        const double tf = a.mat_pen[a.face_material[s.faces[j - 1]]];
+        for (int c = 0; c < 3; ++c) E[c] = cscl(tf, E[c]);
+        continue;
+      }
+      const double4 pl = s.pl[j - 1];
+      const D3 n = {pl.x, pl.y, pl.z};
+      const D3 ki = normed(s.pt(j) - s.pt(j - 1));
+      const D3 kr = normed(s.pt(j + 1) - s.pt(j));
+      const double cos_t = fabs(dot(ki, n));
+      D3 sp = cross(ki, n);
+      const double sl = len(sp);
+      if (sl < 1e-12) {
+        const D3 ax = fabs(ki.x) < 0.9 ? D3{1, 0, 0} : D3{0, 1, 0};
+        sp = normed(cross(ki, ax));
+      } else {
+        sp = (1.0 / sl) * sp;
+      }
+      const D3 pin = cross(sp, ki), pout = cross(sp, kr);
+      Cx te, tm;
+      fresnel_coeffs(a.materials + 3 * a.face_material[s.faces[j - 1]], f, cos_t, te, tm);
+      const Cx es = cadd(cadd(cscl(sp.x, E[0]), cscl(sp.y, E[1])), cscl(sp.z, E[2]));
+      const Cx ep = cadd(cadd(cscl(pin.x, E[0]), cscl(pin.y, E[1])), cscl(pin.z, E[2]));
+      const Cx cs = cmul(te, es), cp = cmul(tm, ep);
+      E[0] = cadd(cscl(sp.x, cs), cscl(pout.x, cp));
+      E[1] = cadd(cscl(sp.y, cs), cscl(pout.y, cp));
+      E[2] = cadd(cscl(sp.z, cs), cscl(pout.z, cp));
+    }
+    const double lam = kC0 / f;
+    const double k0 = 2.0 * kPi * f / kC0;
+    const double mag = a.sqrt_pt * lam / (4.0 * kPi * d) * pow(10.0, -a.atten_db_per_km * d / 20000.0) * gain;
+    double sn, cs;
+    sincos(k0 * d, &sn, &cs);
+    const Cx ph = {mag * cs, -mag * sn};
+    for (int c = 0; c < 3; ++c) {
+      const Cx v = cmul(ph, E[c]);
+      out[2 * c] = v.re;
+      out[2 * c + 1] = v.im;
+    }
+  }
+}
+
+// Validation of a path (Sec. III step 4): every reflection point in its face,
+// and every sub-segment j = 0..order unoccluded (by triangles outside its end
+// faces).
+template <int kLanes>
+__device__ __forceinline__ bool outside_face(const RefineArgs& a, const RefineCand& s, int j, int gl, uint64_t gmask) {
+  const double4 pl = s.pl[j - 1];
+  const bool inside = in_face(a, s.faces[j - 1], s.pt(j), D3{pl.x, pl.y, pl.z}, gl, kLanes);
+  return (__ballot(inside) & gmask) == 0;
+}
+
+template <int kLanes>
+__device__ __forceinline__ void begin_segment(const RefineCand& s, int j, Occlusion<kLanes>& o) {
+  o.begin(s.pt(j), s.pt(j + 1), j >= 1 ? s.faces[j - 1] : -1, j + 1 <= s.order ? s.faces[j] : -1);
+}
+
+// The outputs of candidate u but its field, which is cleared here for a path
+// found invalid; lane gl of n.
+__device__ __forceinline__ void refine_outputs(const RefineArgs& a, uint32_t u, const RefineCand& s, bool ok, int gl, int n) {
+  D3 aod = {0, 0, 0}, aoa = {0, 0, 0};
+  if (ok) {
+    aod = normed(s.pt(1) - s.pt(0));
+    aoa = normed(s.pt(s.order) - s.pt(s.order + 1));
+  }
+  if (gl == 0) {
+    a.valid[u] = ok ? 1 : 0;
+    a.tau[u] = ok ? s.d / kC0 : 0.0;
+    if (!ok) a.length[u] = 0.0;
+    a.aod[3 * u] = aod.x; a.aod[3 * u + 1] = aod.y; a.aod[3 * u + 2] = aod.z;
+    a.aoa[3 * u] = aoa.x; a.aoa[3 * u + 1] = aoa.y; a.aoa[3 * u + 2] = aoa.z;
+  }
+  if (!ok)
+    for (int fi = gl; fi < a.n_freqs; fi += n)
+      for (int k = 0; k < 6; ++k) a.amp[((size_t)u * a.n_freqs + fi) * 6 + k] = 0.0;
+}
+
+// Refinement of the unique candidates, a block of four wavefronts for each (one
+// per SIMD, so four blocks share a compute unit): lane 0 of wavefront 0 computes
+// the geometry, then the wavefronts draw the tasks (a validation per
+// sub-segment, and the field) in a fixed order from an LDS counter (wavefront w
 // starts with position w): the sub-segments longest first, the field at
-// position 1, so wavefront 1 computes it and then writes the outputs once
-// every task is done (a path found invalid is zeroed then).
+// position 1, so wavefront 1 computes it and then writes the outputs once every
+// task is done (a path found invalid is zeroed then).
 constexpr int kRefineWaves = 4;
 
 __global__ __launch_bounds__(kRefineWaves * kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void k_refine(RefineArgs a) {
-  __shared__ double sP[(kMaxK + 2) * 3];      // transmitter, reflection points, receiver
-  __shared__ D3 simg[kMaxK + 1];             // images of the transmitter
-  __shared__ int sfaces[kMaxK];              // face ids (transmission flag cleared)
-  __shared__ uint32_t stmask;                 // bit j - 1: interaction j transmits
-  __shared__ int sorder, sok, sfail;
-  __shared__ double sd;
-  __shared__ double4 spl[kMaxK];              // planes of the faces
+  __shared__ RefineCand s;
   __shared__ uint32_t stk[kRefineWaves][kCheckStack];   // each wavefront's occlusion stack
-  __shared__ int snext;                                   // next free task
-  __shared__ int stask[kMaxK + 2];                        // the tasks in the order they are drawn
-  const uint32_t u = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  __shared__ int snext, sfail;                          // next free task, a task failed
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   const int K = a.K;
-  // the decoded candidate (pair, order, faces: written by the
-  // de-duplication) is loaded while the count is; the arrays hold an entry
-  // for every block, and entries past the count are never used
-  int order0 = 0, pair = 0, face = -1;
+  // the decoded candidate is loaded while the count is (the arrays hold an
+  // entry for every block; entries past the count go unused)
+  const uint32_t u = blockIdx.x;
+  int order0 = 0, pair = 0, face = 0;
   if (w == 0) {
     order0 = a.order[u];
     pair = a.pair[u];
     if (lane < K) face = a.faces[(size_t)u * K + lane];
   }
   if (u >= *a.n_unique) return;   // uniform over the block
-  // ---- 1. geometry: lane j takes face j and loads its plane, lane 0 then
-  // runs the image method on LDS copies
   if (w == 0) {
-    const uint64_t tm = __ballot(lane < order0 && (face & kTransmit));
+    const uint32_t tm = (uint32_t)__ballot(lane < order0 && (face & kTransmit));
     if (lane < order0) {
-      sfaces[lane] = face & kFaceMask;
-      spl[lane] = a.plane[face & kFaceMask];
+      s.faces[lane] = face & kFaceMask;
+      s.pl[lane] = a.plane[face & kFaceMask];
     }
     wave_sync();
     if (lane == 0) {
-      const int tx = pair / a.n_rx, rx = pair - tx * a.n_rx;
-      const D3 T = fvec(a.tx, tx), R = fvec(a.rx, rx);
-      stmask = (uint32_t)tm;
-      sP[0] = T.x; sP[1] = T.y; sP[2] = T.z;
-      sP[3 * (order0 + 1)] = R.x; sP[3 * (order0 + 1) + 1] = R.y; sP[3 * (order0 + 1) + 2] = R.z;
-      // the images, forward once (reflect_image), kept in LDS for the walk
-      D3 im = T;
-      simg[0] = im;
-      for (int j = 1; j <= order0; ++j) {
-        if (!((tm >> (j - 1)) & 1ull)) im = reflect_image(im, spl[j - 1]);
-        simg[j] = im;
-      }
-      bool ok = image_walk(
-          R, order0, [&](int j) { return simg[j]; }, [&](int j) { return spl[j]; },
-          [&](int j, D3 q) {
-            sP[3 * j] = q.x; sP[3 * j + 1] = q.y; sP[3 * j + 2] = q.z;
-            return true;
-          },
-          sd);
-      ok = ok && !through_opaque(a, sfaces, order0, (uint32_t)tm);
-      double* P = a.pts + (size_t)u * (K + 2) * 3;
-      for (int j = 0; j < 3 * (order0 + 2); ++j) P[j] = sP[j];
-      a.length[u] = sd;
-      sorder = order0;
-      sok = ok ? 1 : 0;
+      refine_geometry(a, u, pair, order0, tm, s);
       sfail = 0;
-      // the task order: the sub-segments longest first (an occlusion query's
-      // cost grows with the length it crosses), the field second, so that
-      // wavefront 1 always computes it; tasks 0..3 go to wavefronts 0..3
-      int n_seg = 0;
-      double seg_len[kMaxK + 1];
-      for (int j = 0; j <= order0; ++j) {
-        const double dx = sP[3 * j + 3] - sP[3 * j], dy = sP[3 * j + 4] - sP[3 * j + 1],
-                     dz = sP[3 * j + 5] - sP[3 * j + 2];
-        const double l2 = dx * dx + dy * dy + dz * dz;
-        int i = n_seg++;
-        for (; i > 0 && seg_len[i - 1] < l2; --i) {
-          seg_len[i] = seg_len[i - 1];
-          stask[i + (i >= 1 ? 1 : 0)] = stask[i - 1 + (i - 1 >= 1 ? 1 : 0)];
-        }
-        seg_len[i] = l2;
-        stask[i + (i >= 1 ? 1 : 0)] = j;
-      }
-      stask[1] = order0 + 1;
       snext = kRefineWaves;
     }
   }
   __syncthreads();
-  const int order = sorder;
-  bool ok = sok != 0;
-  auto pt = [&](int j) { return D3{sP[3 * j], sP[3 * j + 1], sP[3 * j + 2]}; };
+  const bool walked = s.ok != 0;
   // task positions are drawn in increasing order, each once: position 1 is
   // the field (wavefront 1 first), the others are sub-segments
-  const int n_tasks = ok ? order + 2 : 0;
+  const int n_tasks = walked ? s.order + 2 : 0;
   int t = w;   // uniform over the wavefront
   auto draw = [&]() {
     int next = 0;
@@ -854,77 +968,18 @@ void k_refine(RefineArgs a) {
     t = __shfl(next, 0);
   };
   if (t == 1 && n_tasks > 1) {
-    // ---- 3. the field, one lane per frequency (a path found invalid is
-    // zeroed once every task is done)
-    const double d = sd;
-    const D3 aod = normed(pt(1) - pt(0));
-    const double rho = sqrt(aod.x * aod.x + aod.y * aod.y);
-    const D3 e0 = rho > 0 ? D3{aod.z * aod.x / rho, aod.z * aod.y / rho, -rho} : D3{aod.z, 0.0, 0.0};
-    const double gain = pattern_gain(a.pat, aod);
-    for (int fi = lane; fi < a.n_freqs; fi += kWave) {
-      const double f = a.freqs[fi];
-      double* out = a.amp + ((size_t)u * a.n_freqs + fi) * 6;
-      Cx E[3] = {{e0.x, 0}, {e0.y, 0}, {e0.z, 0}};
-      for (int j = 1; j <= order; ++j) {
-        if ((stmask >> (j - 1)) & 1u) {
-          // transmission: the penetration loss of the face's material
-          // (Table II), polarisation and direction unchanged
-          const double tf = a.mat_pen[a.face_material[sfaces[j - 1]]];
-          for (int c = 0; c < 3; ++c) E[c] = cscl(tf, E[c]);
-          continue;
-        }
-        const double4 pl = spl[j - 1];
-        const D3 n = {pl.x, pl.y, pl.z};
-        const D3 ki = normed(pt(j) - pt(j - 1));
-        const D3 kr = normed(pt(j + 1) - pt(j));
-        const double cos_t = fabs(dot(ki, n));
-        D3 s = cross(ki, n);
-        const double sl = len(s);
-        if (sl < 1e-12) {
-          const D3 ax = fabs(ki.x) < 0.9 ? D3{1, 0, 0} : D3{0, 1, 0};
-          s = normed(cross(ki, ax));
-        } else {
-          s = (1.0 / sl) * s;
-        }
-        const D3 pin = cross(s, ki), pout = cross(s, kr);
-        Cx te, tm;
-        fresnel_coeffs(a.materials + 3 * a.face_material[sfaces[j - 1]], f, cos_t, te, tm);
-        const Cx es = cadd(cadd(cscl(s.x, E[0]), cscl(s.y, E[1])), cscl(s.z, E[2]));
-        const Cx ep = cadd(cadd(cscl(pin.x, E[0]), cscl(pin.y, E[1])), cscl(pin.z, E[2]));
-        const Cx cs = cmul(te, es), cp = cmul(tm, ep);
-        E[0] = cadd(cscl(s.x, cs), cscl(pout.x, cp));
-        E[1] = cadd(cscl(s.y, cs), cscl(pout.y, cp));
-        E[2] = cadd(cscl(s.z, cs), cscl(pout.z, cp));
-      }
-      const double lam = kC0 / f;
-      const double k0 = 2.0 * kPi * f / kC0;
-      const double mag = a.sqrt_pt * lam / (4.0 * kPi * d) * pow(10.0, -a.atten_db_per_km * d / 20000.0) * gain;
-      double sn, cs;
-      sincos(k0 * d, &sn, &cs);
-      const Cx ph = {mag * cs, -mag * sn};
-      for (int c = 0; c < 3; ++c) {
-        const Cx v = cmul(ph, E[c]);
-        out[2 * c] = v.re;
-        out[2 * c + 1] = v.im;
-      }
-    }
+    refine_field(a, u, s, lane, kWave);
     draw();
   }
+  Occlusion<kWave> query(a, stk[w], lane, ~0ull);
   while (t < n_tasks) {
-    // ---- 2. validation of sub-segment j: for j >= 1 also reflection point j
-    // against its face
-    const int j = stask[t];
-    const uint64_t all = ~0ull;
-    bool fail = false, fault = false;
-    if (j >= 1) {
-      const int f = sfaces[j - 1];
-      const double4 pl = spl[j - 1];
-      const bool inside = in_face(a, f, pt(j), D3{pl.x, pl.y, pl.z}, lane, kWave);
-      fail = __ballot(inside) == 0;
+    // a sub-segment, and the reflection point it starts from
+    const int j = s.seg[t == 0 ? 0 : t - 1];
+    bool fault = false, fail = j >= 1 && outside_face<kWave>(a, s, j, lane, ~0ull);
+    if (!fail) {
+      begin_segment(s, j, query);
+      while (!fail && query.sp > 0) fail = query.step(fault);
     }
-    const int fa = j >= 1 ? sfaces[j - 1] : -1;
-    const int fb = j + 1 <= order ? sfaces[j] : -1;
-    if (!fail && group_occluded(a, pt(j), pt(j + 1), fa, fb, stk[w], lane, all, fault)) fail = true;
     if (fail && lane == 0) sfail = 1;
     if (fault && lane == 0) atomicOr(a.err, DCEM_ERR_STACK);
     draw();
@@ -932,23 +987,57 @@ void k_refine(RefineArgs a) {
   __syncthreads();
   // the outputs, by the wavefront that wrote the field (wavefront 0 when
   // there was none)
-  if (w != (ok ? 1 : 0)) return;
-  ok = ok && sfail == 0;
-  D3 aod = {0, 0, 0}, aoa = {0, 0, 0};
-  if (ok) {
-    aod = normed(pt(1) - pt(0));
-    aoa = normed(pt(order) - pt(order + 1));
+  if (w == (walked ? 1 : 0)) refine_outputs(a, u, s, walked && sfail == 0, lane, kWave);
+}
+
+// The same for long lists: 16 lanes for each candidate, four per wavefront, first
+// the reflection points, then the sub-segments until one is occluded, then
+// the field of the valid ones.
+constexpr int kRefineLanes = 16, kRefineGroups = kRefineWaves * kWave / kRefineLanes;
+// Candidates given a block each.  A block answers one candidate sooner, a
+// wavefront of four wastes less: 550 candidates of the urban scene take 22 and 61
+// us, 3165 58 and 56, 5123 92 and 62; 2500 of a 120000-triangle city 33 and 120;
+// 12136 and 40126 of the office 288 and 83, 567 and 166 (a third of that was
+// blocks past the count of a list sized by its captures).  Bound by the FP64
+// issue of the occlusion tests.
+constexpr int64_t kRefineSpread = 4096;
+
+__global__ __launch_bounds__(kRefineWaves * kWave) __attribute__((amdgpu_waves_per_eu(4)))
+void k_refine_many(RefineArgs a) {
+  __shared__ RefineCand cand[kRefineGroups];
+  __shared__ uint32_t stk[kRefineGroups][kCheckStack];   // each query's occlusion stack
+  const int lane = threadIdx.x & (kWave - 1);
+  const int gl = lane & (kRefineLanes - 1), g = threadIdx.x / kRefineLanes, g0 = lane - gl;
+  const uint64_t gmask = ((1ull << kRefineLanes) - 1ull) << g0;
+  const uint32_t n = *a.n_unique;
+  RefineCand& s = cand[g];
+  const uint32_t u = blockIdx.x * kRefineGroups + g;
+  const bool have = u < n;
+  const int order = have ? a.order[u] : 0;
+  const int pair = have ? a.pair[u] : 0;
+  const int face = gl < order ? a.faces[(size_t)u * a.K + gl] : 0;
+  const uint32_t tm = (uint32_t)((__ballot(face & kTransmit) & gmask) >> g0);
+  if (gl < order) {
+    s.faces[gl] = face & kFaceMask;
+    s.pl[gl] = a.plane[face & kFaceMask];
   }
-  if (lane == 0) {
-    a.valid[u] = ok ? 1 : 0;
-    a.tau[u] = ok ? sd / kC0 : 0.0;
-    if (!ok) a.length[u] = 0.0;
-    a.aod[3 * u] = aod.x; a.aod[3 * u + 1] = aod.y; a.aod[3 * u + 2] = aod.z;
-    a.aoa[3 * u] = aoa.x; a.aoa[3 * u + 1] = aoa.y; a.aoa[3 * u + 2] = aoa.z;
+  wave_sync();
+  if (have && gl == 0) refine_geometry(a, u, pair, order, tm, s);
+  wave_sync();
+  if (have) {
+    bool ok = s.ok != 0, fault = false;
+    for (int j = 1; ok && j <= order; ++j) ok = !outside_face<kRefineLanes>(a, s, j, gl, gmask);
+    // the wavefront's four queries step together, each going on to its
+    // candidate's next sub-segment by itself
+    Occlusion<kRefineLanes> query(a, stk[g], lane, gmask);
+    for (int i = 0; ok && (query.sp > 0 || i <= order);) {
+      if (query.sp == 0) begin_segment(s, s.seg[i++], query);
+      if (query.sp > 0) ok = !query.step(fault);
+    }
+    if (fault && gl == 0) atomicOr(a.err, DCEM_ERR_STACK);
+    if (ok) refine_field(a, u, s, gl, kRefineLanes);
+    refine_outputs(a, u, s, ok, gl, kRefineLanes);
   }
-  if (!ok)
-    for (int fi = lane; fi < a.n_freqs; fi += kWave)
-      for (int k = 0; k < 6; ++k) a.amp[((size_t)u * a.n_freqs + fi) * 6 + k] = 0.0;
 }
 
 
@@ -1894,7 +1983,7 @@ hipError_t build_visited_candidates(dcem_ctx* c, bool los, bool& too_many) {
   return hipGetLastError();
 }
 
-void launch_refine(dcem_ctx* c) {
+void launch_refine(dcem_ctx* c, int64_t expected) {
   const int64_t n = c->path_cap;
   if (n == 0) return;
   RefineArgs a;
@@ -1931,7 +2020,11 @@ void launch_refine(dcem_ctx* c) {
   a.pts = ptr<double>(c->path_pts);
   a.counters = c->cnt_dev;
   a.err = c->err_dev;
-  hipLaunchKernelGGL(k_refine, dim3((unsigned)n), dim3(kRefineWaves * kWave), 0, c->stream, a);
+  if (expected <= kRefineSpread)
+    hipLaunchKernelGGL(k_refine, dim3((unsigned)n), dim3(kRefineWaves * kWave), 0, c->stream, a);
+  else
+    hipLaunchKernelGGL(k_refine_many, dim3((unsigned)((n + kRefineGroups - 1) / kRefineGroups)),
+                       dim3(kRefineWaves * kWave), 0, c->stream, a);
 }
 
 void launch_power_grad(dcem_ctx* c, uint32_t n_unique, double* g_eps, double* g_sig, double* g_pat) {

@@ -14,6 +14,16 @@
 #include <cfloat>
 
 namespace dcem {
+
+int cu_count(dcem_ctx* c) {
+  if (c->n_cus == 0) {
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, c->device) == hipSuccess) c->n_cus = prop.multiProcessorCount;
+    if (c->n_cus <= 0) c->n_cus = 256;
+  }
+  return c->n_cus;
+}
+
 namespace {
 
 __device__ inline float comp(const float3& v, int k) { return k == 0 ? v.x : (k == 1 ? v.y : v.z); }
@@ -1640,15 +1650,6 @@ __global__ void k_dirs_by_pos(const float* __restrict__ dirs, const uint32_t* __
   out[3 * i] = d[0];
   out[3 * i + 1] = d[1];
   out[3 * i + 2] = d[2];
-}
-
-int cu_count(dcem_ctx* c) {
-  if (c->n_cus == 0) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, c->device) == hipSuccess) c->n_cus = prop.multiProcessorCount;
-    if (c->n_cus <= 0) c->n_cus = 256;
-  }
-  return c->n_cus;
 }
 
 int trace_grid(dcem_ctx* c) {
