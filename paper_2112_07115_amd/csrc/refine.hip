@@ -591,10 +591,10 @@ struct RefineArgs {
   uint32_t* err;
 };
 
-// Is point p inside one of the triangles k0, k0 + step, ... of face f
-// (inclusive)?  2D edge functions on the plane projection that drops the
-// normal's dominant axis.  (k0 = 0, step = 1: inside the face.)
-__device__ __forceinline__ bool in_face(const RefineArgs& a, int f, D3 p, D3 n, int k0 = 0, int step = 1) {
+// Is point p inside one of the triangles begin + k0, begin + k0 + step, ... < end
+// of face_tris, a face's (inclusive)?  2D edge functions on the plane projection
+// that drops the normal's dominant axis.  (k0 = 0, step = 1: inside the face.)
+__device__ __forceinline__ bool in_face(const RefineArgs& a, int begin, int end, D3 p, D3 n, int k0 = 0, int step = 1) {
   const double ax = fabs(n.x), ay = fabs(n.y), az = fabs(n.z);
   const int drop = (ax >= ay && ax >= az) ? 0 : (ay >= az ? 1 : 2);
   auto pr = [drop](D3 v, double& u, double& w) {
@@ -604,7 +604,7 @@ __device__ __forceinline__ bool in_face(const RefineArgs& a, int f, D3 p, D3 n, 
   };
   double pu, pw;
   pr(p, pu, pw);
-  for (int k = a.face_tri_off[f] + k0; k < a.face_tri_off[f + 1]; k += step) {
+  for (int k = begin + k0; k < end; k += step) {
     const Leaf L = a.tri4[a.face_slots[k]];
     const D3 A = {L.v0.x, L.v0.y, L.v0.z}, B = {L.v1.x, L.v1.y, L.v1.z}, C = {L.v2.x, L.v2.y, L.v2.z};
     double au, aw, bu, bw, cu, cw;
@@ -782,11 +782,22 @@ struct RefineCand {
   double4 pl[kMaxK];           // planes of the faces
   double d;                    // path length
   int faces[kMaxK];            // face ids (transmission flag cleared)
+  uint64_t len2[kMaxK + 1];    // the sub-segments' squared lengths (as bits: any values have an order)
   int seg[kMaxK + 1];          // the sub-segments, longest first
+  int tri[kMaxK][2];           // the faces' triangles: their range in face_tris
   int order, ok;
   uint32_t tmask;              // bit j - 1: interaction j transmits
   __device__ D3 pt(int j) const { return D3{P[3 * j], P[3 * j + 1], P[3 * j + 2]}; }
 };
+
+// Face f as s's interaction j: what the geometry and the checks read of it.
+__device__ __forceinline__ void load_face(const RefineArgs& a, int f, RefineCand& s, int j) {
+  const int b = a.face_tri_off[f], e = a.face_tri_off[f + 1];
+  s.faces[j] = f;
+  s.pl[j] = a.plane[f];
+  s.tri[j][0] = b;
+  s.tri[j][1] = e;
+}
 
 // Image-method geometry of candidate u by one lane: image sources through the
 // face planes and reflection points walked back from the receiver, each
@@ -812,24 +823,23 @@ __device__ __forceinline__ void refine_geometry(const RefineArgs& a, uint32_t u,
       },
       s.d);
   ok = ok && !through_opaque(a, s.faces, order, tm);
-  double* P = a.pts + (size_t)u * (a.K + 2) * 3;
-  for (int j = 0; j < 3 * (order + 2); ++j) P[j] = s.P[j];
-  a.length[u] = s.d;
   s.order = order;
   s.ok = ok ? 1 : 0;
-  // the sub-segments, longest first: an occlusion query's cost grows with the
-  // length it crosses
-  double seg_len[kMaxK + 1];
-  for (int j = 0; j <= order; ++j) {
-    const D3 e = s.pt(j + 1) - s.pt(j);
-    const double l2 = dot(e, e);
-    int i = j;
-    for (; i > 0 && seg_len[i - 1] < l2; --i) {
-      seg_len[i] = seg_len[i - 1];
-      s.seg[i] = s.seg[i - 1];
-    }
-    seg_len[i] = l2;
-    s.seg[i] = j;
+}
+
+// The sub-segments of s longest first (an occlusion query's cost grows with the
+// length it crosses), by lanes gl = 0..order of a group.
+__device__ __forceinline__ void refine_segments(RefineCand& s, int order, int gl) {
+  if (gl <= order) {
+    const D3 e = s.pt(gl + 1) - s.pt(gl);
+    s.len2[gl] = (uint64_t)__double_as_longlong(dot(e, e));
+  }
+  wave_sync();
+  if (gl <= order) {
+    const uint64_t l2 = s.len2[gl];
+    int rank = 0;
+    for (int j = 0; j <= order; ++j) rank += s.len2[j] > l2 || (s.len2[j] == l2 && j < gl) ? 1 : 0;
+    s.seg[rank] = gl;
   }
 }
 
@@ -899,7 +909,7 @@ __device__ __forceinline__ void refine_field(const RefineArgs& a, uint32_t u, co
 template <int kLanes>
 __device__ __forceinline__ bool outside_face(const RefineArgs& a, const RefineCand& s, int j, int gl, uint64_t gmask) {
   const double4 pl = s.pl[j - 1];
-  const bool inside = in_face(a, s.faces[j - 1], s.pt(j), D3{pl.x, pl.y, pl.z}, gl, kLanes);
+  const bool inside = in_face(a, s.tri[j - 1][0], s.tri[j - 1][1], s.pt(j), D3{pl.x, pl.y, pl.z}, gl, kLanes);
   return (__ballot(inside) & gmask) == 0;
 }
 
@@ -919,7 +929,7 @@ __device__ __forceinline__ void refine_outputs(const RefineArgs& a, uint32_t u, 
   if (gl == 0) {
     a.valid[u] = ok ? 1 : 0;
     a.tau[u] = ok ? s.d / kC0 : 0.0;
-    if (!ok) a.length[u] = 0.0;
+    a.length[u] = ok ? s.d : 0.0;
     a.aod[3 * u] = aod.x; a.aod[3 * u + 1] = aod.y; a.aod[3 * u + 2] = aod.z;
     a.aoa[3 * u] = aoa.x; a.aoa[3 * u + 1] = aoa.y; a.aoa[3 * u + 2] = aoa.z;
   }
@@ -956,18 +966,18 @@ void k_refine(RefineArgs a) {
   if (u >= *a.n_unique) return;   // uniform over the block
   if (w == 0) {
     const uint32_t tm = (uint32_t)__ballot(lane < order0 && (face & kTransmit));
-    if (lane < order0) {
-      s.faces[lane] = face & kFaceMask;
-      s.pl[lane] = a.plane[face & kFaceMask];
-    }
+    if (lane < order0) load_face(a, face & kFaceMask, s, lane);
     wave_sync();
     if (lane == 0) {
       refine_geometry(a, u, pair, order0, tm, s);
       sfail = 0;
       snext = kRefineWaves;
     }
+    wave_sync();
+    refine_segments(s, order0, lane);
   }
   __syncthreads();
+  if (w == 3 && lane < 3 * (s.order + 2)) a.pts[(size_t)u * (K + 2) * 3 + lane] = s.P[lane];
   const bool walked = s.ok != 0;
   // task positions are drawn in increasing order, each once: position 1 is
   // the field (wavefront 1 first), the others are sub-segments
@@ -1028,14 +1038,14 @@ void k_refine_many(RefineArgs a) {
   const int pair = have ? a.pair[u] : 0;
   const int face = gl < order ? a.faces[(size_t)u * a.K + gl] : 0;
   const uint32_t tm = (uint32_t)((__ballot(face & kTransmit) & gmask) >> g0);
-  if (gl < order) {
-    s.faces[gl] = face & kFaceMask;
-    s.pl[gl] = a.plane[face & kFaceMask];
-  }
+  if (gl < order) load_face(a, face & kFaceMask, s, gl);
   wave_sync();
   if (have && gl == 0) refine_geometry(a, u, pair, order, tm, s);
   wave_sync();
   if (have) {
+    refine_segments(s, order, gl);
+    wave_sync();
+    for (int j = gl; j < 3 * (order + 2); j += kRefineLanes) a.pts[(size_t)u * (a.K + 2) * 3 + j] = s.P[j];
     bool ok = s.ok != 0, fault = false;
     for (int j = 1; ok && j <= order; ++j) ok = !outside_face<kRefineLanes>(a, s, j, gl, gmask);
     // the wavefront's four queries step together, each going on to its
@@ -1373,7 +1383,7 @@ __global__ __launch_bounds__(256) void k_expand(ExpandArgs e, int write) {
                               const int f = fs[j - 1] & kFaceMask;
                               const double4 pl = e.ra.plane[f];
                               const D3 n = {pl.x, pl.y, pl.z};
-                              return in_face_bounds(e.face_box, f, q, n) && in_face(e.ra, f, q, n);
+                              return in_face_bounds(e.face_box, f, q, n) && in_face(e.ra, e.ra.face_tri_off[f], e.ra.face_tri_off[f + 1], q, n);
                             },
                             d);
     }
