@@ -205,35 +205,46 @@ struct RxTree {
 
 // Receivers counting-sorted into kRxCols columns of equal x width (stable in
 // receiver index), for the capture test of the group re-trace: a segment
-// scans only the columns its xy extent covers.  The device evaluates the same
-// column formula in the same FP32 operations.
+// scans only the columns its xy extent covers.  After them the grid of cells
+// that hold receivers, for the captures of kept segments.  The device evaluates
+// the same column and cell formulas in the same FP32 operations.
 hipError_t upload_rx_columns(dcem_ctx* c, const std::vector<float>& rx) {
   const int n = (int)(rx.size() / 3);
-  float x0 = INFINITY, x1 = -INFINITY;
-  for (int i = 0; i < n; ++i) {
-    x0 = std::min(x0, rx[3 * i]);
-    x1 = std::max(x1, rx[3 * i]);
-  }
-  const float scale = x1 > x0 ? (float)kRxCols / (x1 - x0) : 0.0f;
-  auto col = [&](float x) {
-    const float v = std::floor((x - x0) * scale);
-    return (int)std::min(std::max(v, 0.0f), (float)(kRxCols - 1));
+  float lo[2] = {INFINITY, INFINITY}, hi[2] = {-INFINITY, -INFINITY};
+  for (int i = 0; i < n; ++i)
+    for (int a = 0; a < 2; ++a) {
+      lo[a] = std::min(lo[a], rx[3 * i + a]);
+      hi[a] = std::max(hi[a], rx[3 * i + a]);
+    }
+  auto scale_of = [&](int a, int cells) { return hi[a] > lo[a] ? (float)cells / (hi[a] - lo[a]) : 0.0f; };
+  const float scale = scale_of(0, kRxCols), sx = scale_of(0, kRxCells), sy = scale_of(1, kRxCells);
+  auto place = [](float v, float v0, float s, int cells) {
+    const float u = std::floor((v - v0) * s);
+    return (int)std::min(std::max(u, 0.0f), (float)(cells - 1));
   };
+  auto col = [&](float x) { return place(x, lo[0], scale, kRxCols); };
   std::vector<int32_t> start(kRxCols + 1, 0);
   for (int i = 0; i < n; ++i) ++start[col(rx[3 * i]) + 1];
   for (int k = 0; k < kRxCols; ++k) start[k + 1] += start[k];
-  std::vector<float> rec(4 * (size_t)n + (kRxCols + 1));
+  std::vector<float> rec(4 * (size_t)n + (kRxCols + 1) + kRxCells * kRxCells / 32);
   std::vector<int32_t> fill(start.begin(), start.end() - 1);
+  std::vector<uint32_t> bits(kRxCells * kRxCells / 32, 0u);
   for (int i = 0; i < n; ++i) {
     const int at = fill[col(rx[3 * i])]++;
     rec[4 * at] = rx[3 * i];
     rec[4 * at + 1] = rx[3 * i + 1];
     rec[4 * at + 2] = rx[3 * i + 2];
     std::memcpy(&rec[4 * at + 3], &i, 4);
+    const int x = place(rx[3 * i], lo[0], sx, kRxCells), y = place(rx[3 * i + 1], lo[1], sy, kRxCells);
+    bits[(y * kRxCells + x) / 32] |= 1u << (x & 31);
   }
   std::memcpy(&rec[4 * (size_t)n], start.data(), sizeof(int32_t) * (kRxCols + 1));
-  c->rx_col_x0 = x0;
+  std::memcpy(&rec[4 * (size_t)n + kRxCols + 1], bits.data(), sizeof(uint32_t) * bits.size());
+  c->rx_col_x0 = c->rx_cell_x0 = lo[0];
+  c->rx_cell_y0 = lo[1];
   c->rx_col_scale = scale;
+  c->rx_cell_sx = sx;
+  c->rx_cell_sy = sy;
   return upload(c->rx_cols, rec, c->stream);
 }
 

@@ -58,6 +58,7 @@ constexpr int kNodeBits = 27;
 constexpr uint32_t kNoEntry = 0xffffffffu;   // no child to push
 constexpr int kGroup = 16;                   // lanes per query in the group traversals: one DPP row
 constexpr int kGroupStack = 128;             // stack entries per group
+constexpr int kRxCells = 256;                // cells per side of the receivers' grid (captures of kept segments)
 constexpr int kRxCols = 64;                  // x columns of the receivers (group re-trace capture test)
 
 // Order LDS accesses of the lanes of one wavefront.
@@ -219,6 +220,10 @@ struct dcem_ctx {
   void* grad_host = nullptr;   // pinned copy of grad_buf, read back in one transfer
   size_t grad_host_bytes = 0;
   float rx_col_x0 = 0.0f, rx_col_scale = 0.0f;
+  // after the column starts, a bit for every cell of a kRxCells x kRxCells grid
+  // over the targets' xy extent that holds a target; cell of x: clamp(floor((x -
+  // rx_cell_x0) * rx_cell_sx), 0, kRxCells - 1), and likewise of y
+  float rx_cell_x0 = 0.0f, rx_cell_y0 = 0.0f, rx_cell_sx = 0.0f, rx_cell_sy = 0.0f;
   std::vector<double> freqs_host;
   int32_t n_rx_nodes = 0;
   dcem::DevBuf face_log;     // [K+1][n_work] int32 face hit per bounce (-1 miss)

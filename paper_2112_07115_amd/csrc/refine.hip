@@ -1385,7 +1385,7 @@ __device__ __forceinline__ bool expand_walk(const ExpandArgs& e, uint32_t s, uin
 // (a tenth, in an office) are walked again by kExpandLanes lanes each, which
 // share the triangles of a face.  With every lane scanning the triangles of its
 // own faces, up to 120 one by one, the 724000 candidates of an office took 402
-// us (117 now; shared by 8 and 64 lanes 124 and 180) and the 124000 of the urban
+// us (117 now; shared by 8 and 64 lanes 124 and 180) and the 495000 of the urban
 // scene 115 (42 now).
 constexpr int kExpandBlock = 256, kExpandLanes = 16;
 

@@ -214,6 +214,8 @@ struct TraceArgs {
   float rx_cull;        // xy margin of the group kernel's receiver cull (radius plus slack)
   const float4* rx_cols;      // receivers by x column, then the column starts (see dcem_ctx::rx_cols)
   float rx_col_x0, rx_col_scale;
+  const uint32_t* rx_cells;   // cells holding receivers (see dcem_ctx::rx_cols)
+  float rx_cell_x0, rx_cell_y0, rx_cell_sx, rx_cell_sy;
   const uint8_t* restart;     // work-list mode: first segment to trace again
   int64_t n_rays;             // rays per source and branch
   int n_work;
@@ -346,13 +348,10 @@ __device__ inline void add_capture(const TraceArgs& a, uint32_t work, uint32_t t
 
 // Captures of one segment [o, o + tend d] (tend infinite on a miss; th its
 // hit distance): capture spheres whose padded box the segment meets, by their
-// 4-wide tree, then the exact closest-approach test; records appended to the
-// frame's capture list.
-__device__ void capture_segment(const TraceArgs& a, const Ray& r, bool hit, float th, float tend, float dd,
-                                uint32_t work, uint32_t txi, int k, ThreadStack& stack, bool& overflow,
-                                bool& cap_over) {
-  if (!a.capture) return;
-  if (!in_rx_band(a, r, hit, th)) return;
+// 4-wide tree, then the exact closest-approach test, and add(sphere).
+template <class Add>
+__device__ __forceinline__ void capture_walk(const TraceArgs& a, const Ray& r, float tend, float dd, ThreadStack& stack,
+                                             bool& overflow, Add add) {
   int node = 0, sp = 0;
   for (int guard = a.n_rx_nodes + 2; guard > 0; --guard) {
     const Node4 nd = node_in_memory(a.rx_nodes, node);
@@ -365,8 +364,7 @@ __device__ void capture_segment(const TraceArgs& a, const Ray& r, bool hit, floa
         continue;
       if (ch < 0) {
         const int c = ~ch;
-        if (captured(r, tend, dd, a.rx[3 * c], a.rx[3 * c + 1], a.rx[3 * c + 2], a.r2))
-          add_capture(a, work, txi, c, k, cap_over);
+        if (captured(r, tend, dd, a.rx[3 * c], a.rx[3 * c + 1], a.rx[3 * c + 2], a.r2)) add(c);
       } else if (next < 0) {
         next = ch;
       } else if (sp < stack.cap) {
@@ -382,6 +380,36 @@ __device__ void capture_segment(const TraceArgs& a, const Ray& r, bool hit, floa
     node = next;
   }
 }
+
+__device__ void capture_segment(const TraceArgs& a, const Ray& r, bool hit, float th, float tend, float dd,
+                                uint32_t work, uint32_t txi, int k, ThreadStack& stack, bool& overflow,
+                                bool& cap_over) {
+  if (!a.capture || !in_rx_band(a, r, hit, th)) return;
+  capture_walk(a, r, tend, dd, stack, overflow, [&](int c) { add_capture(a, work, txi, c, k, cap_over); });
+}
+
+// xy bounds [x0, x1] x [y0, y1] of the centres of the capture spheres that the
+// segment [o, o + tend d] may meet: those of its part inside the spheres' z band,
+// widened by a.rx_cull (a radius plus slack far above the rounding here).
+struct RxReach {
+  float x0 = -INFINITY, x1 = INFINITY, y0 = -INFINITY, y1 = INFINITY;
+  __device__ RxReach(const TraceArgs& a, const Ray& r, float tend) {
+    float s0 = 0.0f, s1 = tend;
+    if (fabsf(r.d.z) > 1e-20f) {
+      const float rz = __builtin_amdgcn_rcpf(r.d.z);
+      const float a0 = (a.rx_zlo - r.o.z) * rz, a1 = (a.rx_zhi - r.o.z) * rz;
+      s0 = fmaxf(s0, fminf(a0, a1));
+      s1 = fminf(s1, fmaxf(a0, a1));
+    }
+    if (!(s1 < 1e30f)) return;
+    const float xa = fmaf(s0, r.d.x, r.o.x), xb = fmaf(s1, r.d.x, r.o.x);
+    const float ya = fmaf(s0, r.d.y, r.o.y), yb = fmaf(s1, r.d.y, r.o.y);
+    x0 = fminf(xa, xb) - a.rx_cull;
+    x1 = fmaxf(xa, xb) + a.rx_cull;
+    y0 = fminf(ya, yb) - a.rx_cull;
+    y1 = fmaxf(ya, yb) + a.rx_cull;
+  }
+};
 
 // Counts and error flags of a thread, summed into the frame's counters.
 struct ItemCounts {
@@ -837,30 +865,122 @@ __global__ __launch_bounds__(kPacketBlock, kPacketPerSimd) void k_trace_packet(T
 // segment origins, directions and ends, with the arithmetic of the trace
 // kernels (a re-trace would capture exactly these).  The re-trace that
 // follows captures its own segments.
-__global__ __launch_bounds__(kTraceBlock) void k_recapture(TraceArgs a) {
-  __shared__ int stack_mem[kStackLds * kTraceBlock];
-  ThreadStack stack{stack_mem + threadIdx.x, a.stack_spill + blockIdx.x * (size_t)kTraceBlock + threadIdx.x,
-                    (size_t)gridDim.x * kTraceBlock, a.stack_thread, kStackLds, kTraceBlock};
+//
+// Reading the segments takes 208 us for the 45 million of the highway scene
+// (4096 spheres), walking the spheres' tree for every segment that crosses
+// their z band took 630 more, most lanes idle.  So a segment is dropped when no
+// sphere's centre lies in the grid cells (LDS) under its part in the band, and
+// the others are collected and walk the tree 64 at a time, their captures staged
+// in LDS: 838 -> 310 us (414 with an atomic on the list's counter for each, and
+// with four blocks per compute unit).
+constexpr int kRecapBlock = 256;
+constexpr int kRecapStack = 16;     // tree stack entries of a thread in LDS
+constexpr int kRecapPerCu = 5;      // blocks per compute unit (30 KB of LDS each)
+constexpr uint32_t kRecapCaps = 64;  // captures a wavefront stages
+constexpr int kRecapCells = 32;     // cell words looked at for a segment (longer ones walk the tree)
+
+__global__ __launch_bounds__(kRecapBlock) void k_recapture(TraceArgs a) {
+  __shared__ int stack_mem[kRecapStack * kRecapBlock];
+  __shared__ uint32_t cells[kRxCells * kRxCells / 32];
+  __shared__ uint2 queue[kRecapBlock / kWave][2 * kWave];   // (ray, segment) to walk
+  __shared__ Capture caps[kRecapBlock / kWave][kRecapCaps];
+  __shared__ uint32_t n_caps[kRecapBlock / kWave];
+  ThreadStack stack{stack_mem + threadIdx.x, a.stack_spill + blockIdx.x * (size_t)kRecapBlock + threadIdx.x,
+                    (size_t)gridDim.x * kRecapBlock, a.stack_thread, kRecapStack, kRecapBlock};
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  for (int i = threadIdx.x; i < kRxCells * kRxCells / 32; i += kRecapBlock) cells[i] = a.rx_cells[i];
+  if (lane == 0) n_caps[wave] = 0;
+  __syncthreads();
+  auto cell = [](float u) { return (int)fminf(fmaxf(floorf(u), 0.0f), (float)(kRxCells - 1)); };
   bool overflow = false, cap_over = false;
-  const uint32_t n_work = (uint32_t)a.n_work;
-  for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < n_work; w += gridDim.x * blockDim.x) {
-    const int nseg = (int)(a.ray_state[w] & 0x0fu);
-    const int stop = min(nseg, (int)a.restart[w]);
-    const uint32_t vsrc = (uint32_t)(w / (uint64_t)a.n_rays);
-    const uint32_t txi = vsrc / (uint32_t)a.n_branch;
-    const uint32_t tset = a.branch_set[vsrc - txi * (uint32_t)a.n_branch];
-    // a branch records the captures of its segments after its last transmission
-    for (int k = tset ? 32 - __builtin_clz(tset) : 0; k < stop; ++k) {
-      const float4 so = a.seg_o[(size_t)k * a.n_work + w];
-      const float4 sd = a.seg_d[(size_t)k * a.n_work + w];
+  auto segment = [&](uint32_t w, int k, Ray& r) {
+    const float4 so = a.seg_o[(size_t)k * a.n_work + w];
+    const float4 sd = a.seg_d[(size_t)k * a.n_work + w];
+    r.o = make_float3(so.x, so.y, so.z);
+    r.d = make_float3(sd.x, sd.y, sd.z);
+    return so.w;   // its end
+  };
+  // may the segment meet a sphere?
+  auto near = [&](const Ray& r, float tend) {
+    if (!in_rx_band(a, r, tend < INFINITY, tend)) return false;
+    const RxReach reach(a, r, tend);
+    const int x0 = cell((reach.x0 - a.rx_cell_x0) * a.rx_cell_sx), x1 = cell((reach.x1 - a.rx_cell_x0) * a.rx_cell_sx);
+    const int y0 = cell((reach.y0 - a.rx_cell_y0) * a.rx_cell_sy), y1 = cell((reach.y1 - a.rx_cell_y0) * a.rx_cell_sy);
+    const int w0 = x0 / 32, w1 = x1 / 32;
+    if ((w1 - w0 + 1) * (y1 - y0 + 1) > kRecapCells) return true;
+    const uint32_t first = ~0u << (x0 & 31), last = ~0u >> (31 - (x1 & 31));
+    uint32_t any = 0;
+    for (int y = y0; y <= y1; ++y)
+      for (int q = w0; q <= w1; ++q)
+        any |= cells[y * (kRxCells / 32) + q] & (q == w0 ? first : ~0u) & (q == w1 ? last : ~0u);
+    return any != 0;
+  };
+  // the wavefront's captures, appended to the list with one atomic
+  auto flush = [&]() {
+    wave_sync();
+    const uint32_t m = min(n_caps[wave], (uint32_t)kRecapCaps);
+    uint32_t base = 0;
+    if (lane == 0 && m) base = atomicAdd(&a.counters[kCntCaptures], m);
+    base = __builtin_amdgcn_readfirstlane(base);
+    for (uint32_t i = lane; i < m; i += kWave) {
+      if (base + i < a.cap_capacity) a.caps[base + i] = caps[wave][i];
+      else cap_over = true;
+    }
+    wave_sync();
+    if (lane == 0) n_caps[wave] = 0;
+    wave_sync();
+  };
+  int n = 0;   // queued, uniform over the wavefront
+  auto walk = [&](int count) {   // the first `count` queued segments, a lane each
+    wave_sync();
+    if (lane < count) {
+      const uint2 q = queue[wave][lane];
+      const uint32_t w = q.x, vsrc = (uint32_t)(w / (uint64_t)a.n_rays);
       Ray r;
-      r.o = make_float3(so.x, so.y, so.z);
-      r.d = make_float3(sd.x, sd.y, sd.z);
+      const float tend = segment(w, (int)q.y, r);
       setup_ray(r);
-      const bool hit = so.w < INFINITY;
-      capture_segment(a, r, hit, so.w, so.w, dot_dd(r), w, txi, k, stack, overflow, cap_over);
+      const uint32_t txi = vsrc / (uint32_t)a.n_branch;
+      capture_walk(a, r, tend, dot_dd(r), stack, overflow, [&](int c) {
+        const uint32_t at = atomicAdd(&n_caps[wave], 1u);
+        if (at < kRecapCaps) caps[wave][at] = Capture{w, ((txi * (uint32_t)a.n_rx + (uint32_t)c) << 4) | q.y};
+        else add_capture(a, w, txi, c, (int)q.y, cap_over);
+      });
+    }
+    wave_sync();
+    if (n_caps[wave] > kRecapCaps / 2) flush();
+    const uint2 rest = queue[wave][kWave + lane];
+    wave_sync();
+    queue[wave][lane] = rest;
+    n -= count;
+  };
+  const uint32_t n_work = (uint32_t)a.n_work, n_waves = gridDim.x * (kRecapBlock / kWave);
+  for (uint64_t w0 = (uint64_t)(blockIdx.x * (kRecapBlock / kWave) + wave) * kWave; w0 < n_work; w0 += (uint64_t)n_waves * kWave) {
+    const bool mine = w0 + lane < n_work;
+    const uint32_t w = mine ? (uint32_t)w0 + lane : 0u;
+    int k = 0, stop = 0;
+    if (mine) {
+      stop = min((int)(a.ray_state[w] & 0x0fu), (int)a.restart[w]);
+      if (a.n_branch > 1) {
+        // a branch records the captures of its segments after its last transmission
+        const uint32_t tset = a.branch_set[(uint32_t)(w / (uint64_t)a.n_rays) % (uint32_t)a.n_branch];
+        if (tset) k = 32 - __builtin_clz(tset);
+      }
+    }
+    for (; __ballot(k < stop); ++k) {
+      bool go = false;
+      if (k < stop) {
+        Ray r;
+        const float tend = segment(w, k, r);
+        go = near(r, tend);
+      }
+      const uint64_t m = __ballot(go);
+      if (go) queue[wave][n + __popcll(m & ((1ull << lane) - 1ull))] = make_uint2(w, (uint32_t)k);
+      n += __popcll(m);
+      if (n >= kWave) walk(kWave);
     }
   }
+  if (n > 0) walk(n);
+  flush();
   if (overflow) atomicOr(a.err, DCEM_ERR_STACK);
   if (cap_over) atomicOr(a.err, DCEM_ERR_CAPTURES);
 }
@@ -1202,33 +1322,15 @@ __global__ __launch_bounds__(kWaveBlock) void k_trace_wave(TraceArgs a) {
     const float za = r.o.z;
     const float zb = hit ? __fmaf_rn(th, r.d.z, r.o.z) : (r.d.z > 0 ? INFINITY : (r.d.z < 0 ? -INFINITY : r.o.z));
     if (a.capture && fmaxf(za, zb) >= a.rx_zlo && fminf(za, zb) <= a.rx_zhi) {
-      // cull by the xy bounds of the segment's part inside the receivers' z
-      // band: a sphere the segment meets has its centre within a radius of
-      // that part (rx_cull adds slack far above the rounding here)
-      float bx0 = -INFINITY, bx1 = INFINITY, by0 = -INFINITY, by1 = INFINITY;
-      float s0 = 0.0f, s1 = tend;
-      if (fabsf(r.d.z) > 1e-20f) {
-        const float rz = __builtin_amdgcn_rcpf(r.d.z);
-        const float a0 = (a.rx_zlo - r.o.z) * rz, a1 = (a.rx_zhi - r.o.z) * rz;
-        s0 = fmaxf(s0, fminf(a0, a1));
-        s1 = fminf(s1, fmaxf(a0, a1));
-      }
-      if (s1 < 1e30f) {
-        const float xa = fmaf(s0, r.d.x, r.o.x), xb = fmaf(s1, r.d.x, r.o.x);
-        const float ya = fmaf(s0, r.d.y, r.o.y), yb = fmaf(s1, r.d.y, r.o.y);
-        bx0 = fminf(xa, xb) - a.rx_cull;
-        bx1 = fmaxf(xa, xb) + a.rx_cull;
-        by0 = fminf(ya, yb) - a.rx_cull;
-        by1 = fmaxf(ya, yb) + a.rx_cull;
-      }
+      const RxReach reach(a, r, tend);
       // receivers of the columns the box covers (one more on each side)
       int c0 = 0, c1 = a.n_rx;
-      if (bx1 < INFINITY) {
-        c0 = rx_col[max(rx_column(bx0) - 1, 0)];
-        c1 = rx_col[min(rx_column(bx1) + 1, kRxCols - 1) + 1];
+      if (reach.x1 < INFINITY) {
+        c0 = rx_col[max(rx_column(reach.x0) - 1, 0)];
+        c1 = rx_col[min(rx_column(reach.x1) + 1, kRxCols - 1) + 1];
       }
       auto test_rx = [&](const float4 q) {
-        if (q.x < bx0 || q.x > bx1 || q.y < by0 || q.y > by1) return;
+        if (q.x < reach.x0 || q.x > reach.x1 || q.y < reach.y0 || q.y > reach.y1) return;
         if (captured(r, tend, dd, q.x, q.y, q.z, a.r2)) {
           Capture cp;
           cp.work = work;
@@ -1698,6 +1800,11 @@ TraceArgs trace_args(dcem_ctx* c, bool all_rays, bool keep_cache, uint32_t n_pre
   a.rx_cols = ptr<float4>(c->rx_cols);
   a.rx_col_x0 = c->rx_col_x0;
   a.rx_col_scale = c->rx_col_scale;
+  a.rx_cells = ptr<uint32_t>(c->rx_cols) + 4 * (size_t)c->n_tgt + kRxCols + 1;
+  a.rx_cell_x0 = c->rx_cell_x0;
+  a.rx_cell_y0 = c->rx_cell_y0;
+  a.rx_cell_sx = c->rx_cell_sx;
+  a.rx_cell_sy = c->rx_cell_sy;
   a.n_rays = c->n_rays;
   a.n_work = (int)n_work;
   a.n_src = c->n_src;
@@ -1816,8 +1923,9 @@ void launch_recapture(dcem_ctx* c) {
   TraceArgs a = trace_args(c, false, true, 0u);
   a.stack_spill = ptr<int>(c->stack_spill);
   const int64_t n_work = (int64_t)c->n_src * c->n_branch * c->n_rays;
-  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(trace_grid(c), (n_work + kTraceBlock - 1) / kTraceBlock));
-  hipLaunchKernelGGL(k_recapture, dim3(grid), dim3(kTraceBlock), 0, c->stream, a);
+  const int grid = (int)std::max<int64_t>(
+      1, std::min<int64_t>((int64_t)cu_count(c) * kRecapPerCu, (n_work + kRecapBlock - 1) / kRecapBlock));
+  hipLaunchKernelGGL(k_recapture, dim3(grid), dim3(kRecapBlock), 0, c->stream, a);
 }
 
 hipError_t prepare_trace(dcem_ctx* c) {
@@ -1828,7 +1936,7 @@ hipError_t prepare_trace(dcem_ctx* c) {
   if (e != hipSuccess) return e;
   const size_t packet =
       (size_t)(kStackSize - kPacketStack) * kPacketBlock * (size_t)std::max(cu_count(c) * kPacketPerSimd, 16);
-  const size_t recapture = (size_t)kStackSpill * kTraceBlock * (size_t)std::max(trace_grid(c), 16);
+  const size_t recapture = (size_t)(kStackSize - kRecapStack) * kRecapBlock * (size_t)cu_count(c) * kRecapPerCu;
   return ensure(c->stack_spill, sizeof(int) * std::max(packet, recapture));
 }
 
