@@ -506,6 +506,7 @@ void dcem_destroy(dcem_ctx* c) {
   for (DevBuf* b : c->buffers()) release(*b);
   if (c->host_block) (void)hipHostFree(c->host_block);
   if (c->grad_host) (void)hipHostFree(c->grad_host);
+  if (c->path_stage) (void)hipHostFree(c->path_stage);
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
   if (c->ev_copy) (void)hipEventDestroy(c->ev_copy);
@@ -1292,6 +1293,32 @@ dcem_status dcem_get_paths(dcem_ctx* c, int64_t cap, int32_t* keys, uint8_t* val
   if (n_out) *n_out = nu;
   const int64_t n = std::min<int64_t>(nu, cap);
   if (n == 0) return DCEM_OK;
+  const size_t row_doubles = 6 * (size_t)c->n_freqs + 8, row_ints = 4 + (size_t)c->K;
+  const bool packed = (8 * row_doubles + 4 * row_ints + 1) * (size_t)n <= kPathStage;
+  if (packed && !c->path_stage && hipHostMalloc(&c->path_stage, kPathStage, hipHostMallocDefault) != hipSuccess) {
+    c->path_stage = nullptr;   // the arrays are copied one by one then
+    (void)hipGetLastError();
+  }
+  if (packed && c->path_stage) {
+    // a short table: packed by one launch into pinned memory (a copy of each
+    // of the arrays costs some 10 us however short it is: a frame of 65536 rays with
+    // its table of 200 paths 392 -> 291 us; above 1 MB the copies themselves count)
+    const PathPack p = pack_paths(c, c->path_stage, n);
+    HIP_TRY(hipGetLastError(), "pack paths");
+    HIP_TRY(hipStreamSynchronize(c->stream), "synchronize");
+    auto put = [](void* dst, const void* src, size_t bytes) {
+      if (dst) std::memcpy(dst, src, bytes);
+    };
+    put(amp, p.amp, 48 * (size_t)n * c->n_freqs);
+    put(aod, p.aod, 24 * (size_t)n);
+    put(aoa, p.aoa, 24 * (size_t)n);
+    put(length, p.length, 8 * (size_t)n);
+    put(tau, p.tau, 8 * (size_t)n);
+    put(keys, p.keys, 4 * (size_t)n * (3 + c->K));
+    put(first_ray, p.first_ray, 4 * (size_t)n);
+    put(valid, p.valid, (size_t)n);
+    return DCEM_OK;
+  }
   auto get = [&](void* dst, DevBuf& b, size_t bytes) -> hipError_t {
     if (!dst) return hipSuccess;
     return hipMemcpy(dst, b.p, bytes, hipMemcpyDeviceToHost);

@@ -242,6 +242,7 @@ struct dcem_ctx {
   // (128 B), SAH values (256 B), then p_coh and p_inc.
   dcem::DevBuf frame_block;
   void* host_block = nullptr;
+  void* path_stage = nullptr;    // pinned, dcem::kPathStage bytes: short path tables on their way out
   size_t host_block_bytes = 0;
   int64_t n_pow_cap = 0;
   uint32_t* cnt_dev = nullptr;
@@ -418,6 +419,15 @@ hipError_t prepare_small_candidates(dcem_ctx* c);
 bool small_path_fits(const dcem_ctx* c);
 int64_t small_path_capacity();
 hipError_t ensure_paths(dcem_ctx* c, int64_t n);
+// A frame's path table as dcem_get_paths returns it, packed into `stage`
+// (pinned host memory, kPathStage bytes) by one launch; n rows.
+constexpr size_t kPathStage = 1 << 20;
+struct PathPack {
+  double *amp, *aod, *aoa, *length, *tau;
+  int32_t *keys, *first_ray;
+  uint8_t* valid;
+};
+PathPack pack_paths(dcem_ctx* c, void* stage, int64_t n);
 // expected: candidates, roughly (any number is refined)
 void launch_refine(dcem_ctx* c, int64_t expected);
 void launch_reduce(dcem_ctx* c);

@@ -2084,6 +2084,58 @@ void launch_refine(dcem_ctx* c, int64_t expected) {
                        dim3(kRefineWaves * kWave), 0, c->stream, a);
 }
 
+namespace {
+
+__global__ __launch_bounds__(256) void k_pack_paths(PathPack in, PathPack out, const int32_t* __restrict__ pair,
+                                                    const uint8_t* __restrict__ order,
+                                                    const int32_t* __restrict__ faces, uint32_t n, uint32_t n_amp,
+                                                    int K, int n_rx) {
+  const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (uint32_t i = i0; i < n_amp; i += step) out.amp[i] = in.amp[i];
+  for (uint32_t i = i0; i < 3 * n; i += step) {
+    out.aod[i] = in.aod[i];
+    out.aoa[i] = in.aoa[i];
+  }
+  for (uint32_t u = i0; u < n; u += step) {
+    out.length[u] = in.length[u];
+    out.tau[u] = in.tau[u];
+    out.first_ray[u] = in.first_ray[u];
+    out.valid[u] = in.valid[u];
+    int32_t* row = out.keys + (size_t)u * (3 + K);
+    const int32_t pr = pair[u], tx = pr / n_rx, ord = order[u];
+    row[0] = tx;
+    row[1] = pr - tx * n_rx;
+    row[2] = ord;
+    for (int j = 0; j < K; ++j) {
+      const int32_t fe = faces[(size_t)u * K + j];
+      // a transmission through face f is reported as -2 - f
+      row[3 + j] = j >= ord ? -1 : ((fe & kTransmit) ? -2 - (fe & kFaceMask) : fe);
+    }
+  }
+}
+
+}  // namespace
+
+PathPack pack_paths(dcem_ctx* c, void* stage, int64_t n) {
+  const PathPack in{ptr<double>(c->path_amp), ptr<double>(c->path_aod), ptr<double>(c->path_aoa),
+                    ptr<double>(c->path_len), ptr<double>(c->path_tau), nullptr,
+                    ptr<int32_t>(c->first_ray), ptr<uint8_t>(c->path_valid)};
+  PathPack out;
+  out.amp = static_cast<double*>(stage);
+  out.aod = out.amp + 6 * n * c->n_freqs;
+  out.aoa = out.aod + 3 * n;
+  out.length = out.aoa + 3 * n;
+  out.tau = out.length + n;
+  out.keys = reinterpret_cast<int32_t*>(out.tau + n);
+  out.first_ray = out.keys + n * (3 + c->K);
+  out.valid = reinterpret_cast<uint8_t*>(out.first_ray + n);
+  const uint32_t n_amp = (uint32_t)(6 * n * c->n_freqs);
+  const unsigned blocks = (unsigned)std::min<int64_t>((std::max<int64_t>(n_amp, 3 * n) + 255) / 256, 256);
+  hipLaunchKernelGGL(k_pack_paths, dim3(blocks), dim3(256), 0, c->stream, in, out, ptr<int32_t>(c->pair_range),
+                     ptr<uint8_t>(c->path_order), ptr<int32_t>(c->path_faces), (uint32_t)n, n_amp, c->K, c->n_rx);
+  return out;
+}
+
 void launch_power_grad(dcem_ctx* c, uint32_t n_unique, double* g_eps, double* g_sig, double* g_pat) {
   const int n_pairs = c->n_tx * c->n_rx;
   hipLaunchKernelGGL(k_power_grad, dim3((n_pairs * 64 + 255) / 256), dim3(256), 0, c->stream,
