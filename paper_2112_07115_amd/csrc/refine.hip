@@ -130,11 +130,14 @@ __global__ void k_keys(const Capture* __restrict__ caps, const uint32_t* __restr
 // the decoded candidate (see UniqueOut).  The set of keys, their order and
 // the lowest ray per key equal those of a stable sort of all captures
 // followed by run heads.
-constexpr int kSmallN = 2048;
+// As many captures as the workgroup's LDS takes (137 KB; a list expected to
+// fill three quarters of it goes the long way): 2200 captures take 22 us, the key,
+// sort, head and record launches of a longer list 60.
+constexpr int kSmallN = 3072;
 constexpr int kSmallW = 3;
 constexpr int kCandBlock = 1024;
 constexpr int kCandPer = kSmallN / kCandBlock;   // captures per thread
-constexpr int kHashSlots = 2 * kSmallN;          // load factor <= 1/2
+constexpr int kHashSlots = 4096;                 // load factor <= 3/4
 constexpr int kSlotsPer = kHashSlots / kCandBlock;
 constexpr int kBuckets = 2048;
 constexpr int kBucketsPer = kBuckets / kCandBlock;
@@ -206,11 +209,16 @@ __global__ __launch_bounds__(kCandBlock) void k_small_candidates(
   __shared__ uint32_t kk[kSmallW][kSmallN];              // key words per capture
   __shared__ uint32_t cpair[kSmallN];                    // (tx, rx) pair per capture
   __shared__ uint32_t cwork[kSmallN];                    // lowest ray of the key, at its chosen capture
-  __shared__ uint32_t slot_idx[kHashSlots];              // a capture of the slot's key
-  __shared__ unsigned long long slot_best[kHashSlots];   // min (ray << 32 | capture) of the key
+  __shared__ struct {
+    unsigned long long best[kHashSlots];   // min (ray << 32 | capture) of the slot's key
+    uint32_t idx[kHashSlots];              // a capture of the slot's key
+  } slots;
+  unsigned long long* slot_best = slots.best;
+  uint32_t* slot_idx = slots.idx;
+  static_assert(sizeof slots >= sizeof(uint4) * kSmallN, "the unique keys replace the slots");
   __shared__ uint32_t bstart[kBuckets];                  // counts, then exclusive starts
   __shared__ uint32_t wsum[kCandBlock / kWave + 1];
-  uint4* bkey = reinterpret_cast<uint4*>(slot_best);     // after step 2: unique keys by bucket
+  uint4* bkey = reinterpret_cast<uint4*>(&slots);        // after step 2: unique keys by bucket
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   // the records are loaded while their count is (every record below the
   // buffer's capacity is readable; those past the count go unused)

@@ -38,8 +38,8 @@ def test_tree_sizes(n):
     ctx.close()
 
 
-# about 4k, 17k, 100k and 400k captures (fewer take a de-duplication without the sort)
-@pytest.mark.parametrize("radius,n", [(4.0, 100_000), (8.0, 100_000), (8.0, 600_000), (12.0, 1_000_000)])
+# about 2.5k captures, de-duplicated without the sort; 4k, 17k, 100k and 400k
+@pytest.mark.parametrize("radius,n", [(2.0, 240_000), (4.0, 100_000), (8.0, 100_000), (8.0, 600_000), (12.0, 1_000_000)])
 def test_candidate_sizes(radius, n):
     s = scenes.static_toy()
     s = scenes.Scene(**{**s.__dict__, "rx_radius": radius, "n_rays": n, "max_reflections": 3})
