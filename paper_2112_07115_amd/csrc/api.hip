@@ -635,6 +635,16 @@ dcem_status dcem_scene_upload(dcem_ctx* c, const dcem_scene_desc* s) {
     if (ref[f] < 0) return fail(c, DCEM_E_INVALID_ARG, "face %d has no triangle", f);
     if (!(best[f] > 0.0)) return fail(c, DCEM_E_INVALID_ARG, "face %d has only degenerate triangles", f);
   }
+  // does a static face use a vertex that moves with an object?  (The refit then
+  // takes every triangle for one that can move.)
+  bool still_faces = true;
+  {
+    std::vector<bool> moves((size_t)s->n_vertices, false);
+    for (const auto& r : ranges) std::fill(moves.begin() + r.first, moves.begin() + r.second, true);
+    for (size_t t = 0; t < TF.size() && still_faces && !ranges.empty(); ++t)
+      if (FO[TF[t]] < 0) still_faces = !(moves[T[3 * t]] || moves[T[3 * t + 1]] || moves[T[3 * t + 2]]);
+  }
+  c->still_faces = still_faces;
   c->nv = s->n_vertices;
   c->nt = s->n_tris;
   c->nf = nf;

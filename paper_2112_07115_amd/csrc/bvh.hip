@@ -330,14 +330,30 @@ __device__ inline int lcp(const uint32_t* __restrict__ key_hi, const uint32_t* _
   return 64 + __clz((uint32_t)(i ^ j));
 }
 
+constexpr int kKarrasBlock = 256;
+
 // Hierarchy from the sorted Morton codes, one thread per internal node
 // (Karras, "Maximizing parallelism in the construction of BVHs", 2012).
 __global__ void k_karras(const uint32_t* __restrict__ key_hi, const uint32_t* __restrict__ key_lo,
                          const uint32_t* __restrict__ perm, int n,
                          Node* __restrict__ nodes, int32_t* __restrict__ leaf_parent,
-                         int32_t* __restrict__ leaf_tri, int2* __restrict__ range) {
+                         int32_t* __restrict__ leaf_tri, int2* __restrict__ range,
+                         const int32_t* __restrict__ tri_face, const int32_t* __restrict__ face_object,
+                         uint8_t* __restrict__ moves) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) leaf_tri[i] = (int32_t)perm[i];
+  bool moving = false;
+  if (i < n) {
+    leaf_tri[i] = (int32_t)perm[i];
+    moving = face_object[tri_face[perm[i]]] >= 0;
+  }
+  // can a leaf of this block move? (and none of those that would fill the last
+  // refit block)
+  const int any = __syncthreads_or(moving);
+  if (threadIdx.x == 0) {
+    moves[blockIdx.x] = any ? 1 : 0;
+    if (blockIdx.x == gridDim.x - 1)
+      for (unsigned b = gridDim.x; b % (kRefitBlock / kKarrasBlock); ++b) moves[b] = 0;
+  }
   if (i >= n - 1) return;
   int d = (lcp(key_hi, key_lo, perm, n, i, i + 1) - lcp(key_hi, key_lo, perm, n, i, i - 1)) >= 0 ? 1 : -1;
   int dmin = lcp(key_hi, key_lo, perm, n, i, i - d);
@@ -370,8 +386,9 @@ __global__ void k_karras(const uint32_t* __restrict__ key_hi, const uint32_t* __
 }
 
 // Binary nodes whose leaf range spans several refit blocks ("cross" nodes):
-// listed once per build with their list index per node (-1 otherwise) and the
-// list index and slot of their parent (the parent of a cross node is one too).
+// listed once per build with their list index per node (-1 otherwise), the
+// list index and slot of their parent (the parent of a cross node is one too),
+// and in c.w which of their slots are still (see CrossLinks).
 __global__ void k_cross_mark(const int2* __restrict__ range, int n_internal, int32_t* __restrict__ cross_index,
                              int32_t* __restrict__ cross_list, uint32_t* __restrict__ n_cross) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -386,13 +403,23 @@ __global__ void k_cross_mark(const int2* __restrict__ range, int n_internal, int
   cross_list[k] = i;
 }
 
-__global__ void k_cross_parent(const Node* __restrict__ nodes, const int32_t* __restrict__ cross_index,
+__global__ void k_cross_parent(Node* __restrict__ nodes, const int32_t* __restrict__ cross_index,
                                const int32_t* __restrict__ cross_list, const uint32_t* __restrict__ n_cross,
-                               int n_internal, int32_t* __restrict__ cross_parent) {
+                               int n_internal, int32_t* __restrict__ cross_parent, const int2* __restrict__ range,
+                               const uint32_t* __restrict__ moves) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n_internal || k >= (int)*n_cross) return;
-  const int p2 = nodes[cross_list[k]].c.z;
-  cross_parent[k] = p2 < 0 ? -1 : (cross_index[p2 >> 1] << 1) | (p2 & 1);
+  const int4 c = nodes[cross_list[k]].c;
+  cross_parent[k] = c.z < 0 ? -1 : (cross_index[c.z >> 1] << 1) | (c.z & 1);
+  int still = 0;
+  for (int s = 0; s < 2; ++s) {
+    const int kid = s ? c.y : c.x;
+    const int2 rg = kid < 0 ? make_int2(~kid, ~kid) : range[kid];
+    uint32_t any = 0;
+    for (int b = rg.x / kRefitBlock; b <= rg.y / kRefitBlock; ++b) any |= moves[b];
+    still |= any ? 0 : 1 << s;
+  }
+  nodes[cross_list[k]].c.w = still;
 }
 
 __global__ __launch_bounds__(kRefitBlock) void k_refit(RefitArgs a) { refit_block(a, blockIdx.x, gridDim.x); }
@@ -632,6 +659,7 @@ hipError_t build_lbvh(dcem_ctx* c, bool separate_objects) {
   // one spare node: the re-trace reads 48 bytes from a 32-byte slot
   if ((e = ensure(c->nodes4, sizeof(Node4) * (ni + 1))) != hipSuccess) return e;
   if ((e = ensure(c->tri4, sizeof(Leaf) * 4 * (size_t)ni)) != hipSuccess) return e;
+  if ((e = ensure(c->leaf_moves, sizeof(uint32_t) * (size_t)refit_blocks)) != hipSuccess) return e;
   if ((e = ensure(c->bvh2_of4, sizeof(int32_t) * ni)) != hipSuccess) return e;
   if ((e = ensure(c->map4, sizeof(int32_t) * ni)) != hipSuccess) return e;
   if ((e = ensure(c->slot4, sizeof(int32_t) * 2 * (size_t)ni)) != hipSuccess) return e;
@@ -721,9 +749,10 @@ hipError_t tree_from_keys(dcem_ctx* c, int key_words, int key_bits) {
     if ((e = hipMemcpyAsync(c->node_range.p, &rg, sizeof rg, hipMemcpyHostToDevice, c->stream)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
   } else {
-    hipLaunchKernelGGL(k_karras, dim3((nt + 255) / 256), dim3(256), 0, c->stream, key_hi, key_lo, perm, (int)nt,
-                       ptr<Node>(c->nodes), ptr<int32_t>(c->leaf_parent), ptr<int32_t>(c->leaf_tri),
-                       ptr<int2>(c->node_range));
+    hipLaunchKernelGGL(k_karras, dim3((nt + kKarrasBlock - 1) / kKarrasBlock), dim3(kKarrasBlock), 0, c->stream, key_hi,
+                       key_lo, perm, (int)nt, ptr<Node>(c->nodes), ptr<int32_t>(c->leaf_parent),
+                       ptr<int32_t>(c->leaf_tri), ptr<int2>(c->node_range), ptr<int32_t>(c->tri_face),
+                       ptr<int32_t>(c->face_object), ptr<uint8_t>(c->leaf_moves));
   }
   uint32_t* info = ptr<uint32_t>(c->tree_info);
   hipLaunchKernelGGL(k_set2, dim3(1), dim3(64), 0, c->stream, info + 2, 0u, info + 3, 0u);
@@ -732,7 +761,8 @@ hipError_t tree_from_keys(dcem_ctx* c, int key_words, int key_bits) {
   hipLaunchKernelGGL(k_cross_mark, dim3((ni + 255) / 256), dim3(256), 0, c->stream, ptr<int2>(c->node_range), ni,
                      cross, cross + ni, info + 2);
   hipLaunchKernelGGL(k_cross_parent, dim3((ni + 255) / 256), dim3(256), 0, c->stream, ptr<Node>(c->nodes), cross,
-                     cross + ni, info + 2, ni, cross + 2 * (size_t)ni);
+                     cross + ni, info + 2, ni, cross + 2 * (size_t)ni, ptr<int2>(c->node_range),
+                     ptr<uint32_t>(c->leaf_moves));
   launch_refit(c, false, c->sah_dev + 0);
   // 4-wide tree: binary nodes at even depth, breadth-first
   uint32_t* dkey = ptr<uint32_t>(c->depth_key);
@@ -802,6 +832,7 @@ RefitArgs make_refit_args(dcem_ctx* c, bool wide, double* sah_out) {
   a.face_ref_tri = ptr<int32_t>(c->face_ref_tri);
   a.nf = c->nf;
   a.plane = ptr<double4>(c->face_plane);
+  a.moves = c->still_faces && c->nt > 1 ? ptr<uint32_t>(c->leaf_moves) : nullptr;
   a.cross_kernel = c->nt > kCrossKernelLeaves;
   return a;
 }

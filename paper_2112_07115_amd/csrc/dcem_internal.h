@@ -195,6 +195,8 @@ struct dcem_ctx {
   dcem::DevBuf cross;                                // refit: nodes spanning refit blocks (index, list, parents, slots)
   dcem::DevBuf tree_info;                            // uint32 [0]: 4-wide nodes, [1]: root leaf-slot mask,
                                                      // [2]: cross nodes, [3], [4]: refit list length and block ticket
+  bool still_faces = false;   // no static face uses a vertex of a moving object
+  dcem::DevBuf leaf_moves;                           // byte per 256 sorted leaves: one of them can move
   dcem::DevBuf tri4;                                 // leaf triangles in slot order (Leaf [n4][4])
   dcem::DevBuf face_build;                           // build scratch: face codes, boxes, keys and order
   // the last full build's keys (in `morton`): grouped by object, and their layout
@@ -298,7 +300,7 @@ struct dcem_ctx {
     return {&ref_vertices, &vertices, &tris, &tri_face, &face_material, &face_object, &materials, &obj_range,
             &face_tri_off, &face_tris, &face_ref_tri, &xf, &obj_box, &face_plane, &tri_slot, &face_slots,
             &nodes, &leaf_slot, &leaf_tri, &leaf_parent, &refit_cnt, &morton, &sort_tmp, &sah_part, &scene_box,
-            &node_range, &nodes4, &bvh2_of4, &map4, &depth_key, &slot4, &cross, &tree_info, &tri4, &face_build,
+            &node_range, &nodes4, &bvh2_of4, &map4, &depth_key, &slot4, &cross, &tree_info, &leaf_moves, &tri4, &face_build,
             &dirs, &dirs_by_pos, &ray_order, &src_pos, &tgt_pos, &freqs, &rx_nodes, &rx_cols, &grad_buf, &face_log, &ray_state,
             &seg_o, &seg_d, &log_tri, &log_t, &log_len, &caps[0], &caps[1], &work_list, &invalid_flag, &stack_spill, &queues, &count_part,
             &frame_block, &cand_keys, &cand_perm, &cand_tmp, &uniq_idx, &first_ray, &path_valid, &path_len,
