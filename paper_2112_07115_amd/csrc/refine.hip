@@ -465,10 +465,6 @@ __global__ __launch_bounds__(256) void k_unique_info(const uint32_t* __restrict_
 }
 
 
-// Products are fused with sums inside one expression only, so that kernels that
-// share these functions get the same bits from them.
-#pragma clang fp contract(on)
-
 struct D3 {
   double x, y, z;
 };
