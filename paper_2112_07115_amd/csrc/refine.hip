@@ -369,7 +369,7 @@ __global__ __launch_bounds__(256) void k_heads(const uint32_t* __restrict__ keys
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   const uint32_t n = min(*n_dev, n_max);
   bool h = false;
-  if (run_min && i < n) run_min[i] = kNoRay;   // nullable: per-run lowest ray ids, filled by k_compact
+  if (i < n) run_min[i] = kNoRay;   // per-run lowest ray ids, filled by k_compact
   if (i < n) {
     h = i == 0;
     if (!h) {
@@ -408,8 +408,8 @@ __global__ __launch_bounds__(1024) void k_scan_small(uint32_t* __restrict__ v, i
   if (threadIdx.x == 1023) *total = part[1023];
 }
 
-// Positions of the run heads (uniq_pos), and with run_min (nullable) the
-// lowest ray id of every run: each wavefront's part of a run enters its lowest
+// Positions of the run heads (uniq_pos) and the lowest ray id of every run, of
+// captures or, with `rays`, of items with these ray ids: each wavefront's part of a run enters its lowest
 // ray into the run's minimum (atomic, so a long run costs no serial walk; one
 // atomic per capture queued on the addresses of long runs: 104 us for the 245000
 // captures of an office frame, now 5).
@@ -419,13 +419,13 @@ __global__ __launch_bounds__(256) void k_compact(const uint8_t* __restrict__ hea
                                                  const uint32_t* __restrict__ n_unique,
                                                  uint32_t* __restrict__ uniq_pos, uint32_t* __restrict__ run_min,
                                                  const uint32_t* __restrict__ perm, const Capture* __restrict__ caps,
-                                                 KeyLayout L) {
+                                                 const uint32_t* __restrict__ rays, KeyLayout L) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   const uint32_t n = min(*n_dev, n_max);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool h = i < n && head[i];
   uint32_t ray = kNoRay;
-  if (run_min && i < n) ray = ray_of(caps[perm[i]].work, L);   // loaded while the heads are counted
+  if (i < n) ray = rays ? rays[perm[i]] : ray_of(caps[perm[i]].work, L);   // loaded while the heads are counted
   const uint64_t m = __ballot(h);
   __shared__ uint32_t wc[4];
   if (lane == 0) wc[wave] = (uint32_t)__popcll(m);
@@ -433,17 +433,15 @@ __global__ __launch_bounds__(256) void k_compact(const uint8_t* __restrict__ hea
   uint32_t off = block_off[blockIdx.x];
   for (int w = 0; w < wave; ++w) off += wc[w];
   if (h) uniq_pos[off + __popcll(m & ((1ull << lane) - 1ull))] = i;
-  if (run_min) {
-    // the lowest ray of each run's part in this wavefront, by the part's first lane
-    const uint64_t after = m & ~((2ull << lane) - 1ull);
-    const int end = after ? __ffsll((unsigned long long)after) - 1 : kWave;
-    for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t v = __shfl_down(ray, o);
-      if (lane + o < end) ray = min(ray, v);
-    }
-    // run index of position i: the heads at or before it, less one
-    if (i < n && (h || lane == 0)) atomicMin(&run_min[off + __popcll(m & ((2ull << lane) - 1ull)) - 1], ray);
+  // the lowest ray of each run's part in this wavefront, by the part's first lane
+  const uint64_t after = m & ~((2ull << lane) - 1ull);
+  const int end = after ? __ffsll((unsigned long long)after) - 1 : kWave;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t v = __shfl_down(ray, o);
+    if (lane + o < end) ray = min(ray, v);
   }
+  // run index of position i: the heads at or before it, less one
+  if (i < n && (h || lane == 0)) atomicMin(&run_min[off + __popcll(m & ((2ull << lane) - 1ull)) - 1], ray);
   if (i == 0) uniq_pos[*n_unique] = n;
 }
 
@@ -1075,10 +1073,9 @@ void k_refine_many(RefineArgs a) {
 //    leading hits, at most K), plus the empty series of every source (the
 //    direct paths).  Item key: words 0..W-1 hold (source, order, faces in path
 //    order) in a candidate key's layout without the receiver field; word W
-//    holds the item's ray id (kNoRay for an empty series), so after one sort
-//    the head of each run of equal series carries the lowest ray visiting it.
-// 2. Sort, run heads, compaction: the unique series, sorted, and per source
-//    the start of its series.
+//    holds the item's ray id (kNoRay for an empty series).
+// 2. Sort on words 0..W-1, run heads, compaction: the unique series, sorted, the
+//    lowest ray visiting each, and per source the start of its series.
 // 3. Expansion: candidate u of the S x n_tgt (series, target) pairs, numbered
 //    in the order of its path key (forward: source-major, then target, then
 //    series; backward: target-major, then series), survives when its
@@ -1195,7 +1192,8 @@ struct SeriesOut {
 __global__ __launch_bounds__(256) void k_series_info(const uint32_t* __restrict__ keys, int64_t stride, KeyLayout S,
                                                      const uint32_t* __restrict__ perm,
                                                      const uint32_t* __restrict__ uniq_pos,
-                                                     const uint32_t* __restrict__ n_series, SeriesOut o) {
+                                                     const uint32_t* __restrict__ n_series,
+                                                     const uint32_t* __restrict__ run_min, SeriesOut o) {
   const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= *n_series) return;
   const uint32_t idx = perm[uniq_pos[s]];
@@ -1204,7 +1202,7 @@ __global__ __launch_bounds__(256) void k_series_info(const uint32_t* __restrict_
   const uint32_t order = key_bits(w, S.W, S.K * S.bf, 4);
   o.src[s] = (int32_t)key_bits(w, S.W, S.K * S.bf + 4, S.bt);
   o.order[s] = (int32_t)order;
-  const uint32_t rid = keys[S.W * stride + idx];
+  const uint32_t rid = run_min[s];
   o.first[s] = rid == kNoRay ? -1 : (int32_t)rid;
   for (int j = 0; j < S.K; ++j)
     o.faces[(size_t)s * S.K + j] = (uint32_t)j < order ? field_face(key_bits(w, S.W, (S.K - 1 - j) * S.bf, S.bf), S.tb) : -1;
@@ -1905,7 +1903,7 @@ hipError_t build_candidates(dcem_ctx* c, bool small, int64_t hint) {
                      run_min);
   hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, c->stream, bcnt, nb, cnt + kCntUnique);
   hipLaunchKernelGGL(k_compact, dim3(nb), dim3(256), 0, c->stream, head, bcnt, n_dev, n_max, cnt + kCntUnique,
-                     ptr<uint32_t>(c->uniq_idx), run_min, perm, ptr<Capture>(c->caps[c->cur_caps]), L);
+                     ptr<uint32_t>(c->uniq_idx), run_min, perm, ptr<Capture>(c->caps[c->cur_caps]), nullptr, L);
   hipLaunchKernelGGL(k_unique_info, dim3(nb), dim3(256), 0, c->stream, keys, (int64_t)n, L, perm,
                      ptr<uint32_t>(c->uniq_idx), cnt + kCntUnique, run_min, unique_out(c));
   if (device_count)
@@ -1965,18 +1963,20 @@ hipError_t build_visited_candidates(dcem_ctx* c, bool los, bool& too_many) {
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
   if (n_items == 0) return hipSuccess;
   n_items = std::min<uint32_t>(n_items, (uint32_t)cap);
-  // sized by the items there are (read above), on the bits of ray ids there are
-  if ((e = radix_sort_perm(c, keys, Wt, 32 + S.bits, sc, n_items, perm, perm + cap, c->stream, cap,
-                           bits_for(n_work))) != hipSuccess)
+  // sized by the items there are (read above); the lowest ray of each run of
+  // equal series is a minimum over the run (sorting on the ray ids as well, for
+  // the run's head to carry it, would take two to four passes more)
+  if ((e = radix_sort_perm(c, keys, S.W, S.bits, sc, n_items, perm, perm + cap, c->stream, cap)) != hipSuccess)
     return e;
+  uint32_t* run_min = perm + cap;   // free after the sort
   const int nbi = (int)((n_items + 255) / 256);
   hipLaunchKernelGGL(k_heads, dim3(nbi), dim3(256), 0, c->stream, keys, (int64_t)cap, S.W, perm, sc, n_items, head,
-                     bcnt, nullptr);
+                     bcnt, run_min);
   hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, c->stream, bcnt, nbi, sc + 1);
   hipLaunchKernelGGL(k_compact, dim3(nbi), dim3(256), 0, c->stream, head, bcnt, sc, n_items, sc + 1,
-                     ptr<uint32_t>(c->uniq_idx), nullptr, nullptr, nullptr, S);
+                     ptr<uint32_t>(c->uniq_idx), run_min, perm, nullptr, keys + S.W * cap, S);
   hipLaunchKernelGGL(k_series_info, dim3(nbi), dim3(256), 0, c->stream, keys, (int64_t)cap, S, perm,
-                     ptr<uint32_t>(c->uniq_idx), sc + 1, so);
+                     ptr<uint32_t>(c->uniq_idx), sc + 1, run_min, so);
   hipLaunchKernelGGL(k_series_starts, dim3((c->n_src + 1 + 255) / 256), dim3(256), 0, c->stream, so.src, sc + 1,
                      c->n_src, start);
   uint32_t n_series = 0;

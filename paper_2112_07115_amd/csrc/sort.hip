@@ -25,19 +25,6 @@ namespace {
 
 constexpr int kDigits = 256;
 
-// Digit pass p of a sort on `bits` key bits of which the low word holds
-// low_bits: its word (from the least significant) and shift.
-struct Passes {
-  int n, n_low;   // passes; those in the least significant word
-  __host__ __device__ Passes(int bits, int low_bits) {
-    const int low = (min_(min_(bits, low_bits), 32) + 7) / 8;
-    n_low = low < 0 ? 0 : low;
-    n = n_low + (bits > 32 ? (bits - 32 + 7) / 8 : 0);
-  }
-  __host__ __device__ static int min_(int a, int b) { return a < b ? a : b; }
-  __host__ __device__ int bit(int p) const { return p < n_low ? 8 * p : 32 + 8 * (p - n_low); }
-};
-
 // Lanes of the wavefront with this lane's digit d (among the lanes of `valid`).
 __device__ inline uint64_t digit_peers(uint64_t valid, uint32_t d) {
   uint64_t peers = valid;
@@ -87,7 +74,7 @@ constexpr int kSmallSort = kSmallThreads * kSmallRounds;
 // in LDS (144 KB).  7 passes over 2200 items of a list sized for 8500 take 32 us,
 // in launches per pass 46 us and eight launch gaps.
 __global__ __launch_bounds__(kSmallThreads) void k_sort_small(const uint32_t* __restrict__ keys, int64_t stride, int W,
-                                                              Passes passes, const uint32_t* __restrict__ n_dev,
+                                                              int passes, const uint32_t* __restrict__ n_dev,
                                                               uint32_t n_max, uint32_t* __restrict__ perm) {
   __shared__ uint32_t sidx[kSmallSort], skey[kSmallSort];
   __shared__ uint32_t cnt[kSmallWaves][kDigits], tmp[kDigits / kWave];
@@ -95,10 +82,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(const uint32_t* __
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int rounds = (int)((n + kSmallThreads - 1) / kSmallThreads);
   const uint32_t base = wave * rounds * kWave + lane;   // this lane's items: every 64th from here
-  for (int p = 0; p < passes.n; ++p) {
-    const int bit = passes.bit(p), shift = bit & 31;
+  for (int p = 0; p < passes; ++p) {
+    const int bit = 8 * p, shift = bit & 31;
     const uint32_t* word = keys + (W - 1 - bit / 32) * stride;
-    const bool fresh = p == 0 || passes.bit(p - 1) / 32 != bit / 32;   // the word is not in LDS yet
+    const bool fresh = p == 0 || 8 * (p - 1) / 32 != bit / 32;   // the word is not in LDS yet
     for (int i = tid; i < kSmallWaves * kDigits; i += kSmallThreads) cnt[0][i] = 0;
     uint32_t idx[kSmallRounds], key[kSmallRounds], rank[kSmallRounds];
 #pragma unroll
@@ -136,7 +123,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(const uint32_t* __
     }
     __syncthreads();
   }
-  for (uint32_t i = tid; i < n; i += kSmallThreads) perm[i] = passes.n ? sidx[i] : i;
+  for (uint32_t i = tid; i < n; i += kSmallThreads) perm[i] = passes ? sidx[i] : i;
 }
 
 constexpr int kThreads = 256, kWaves = kThreads / kWave;
@@ -157,22 +144,27 @@ struct SortScratch {
   }
 };
 
-// Digit totals of every pass, in item order: one pass over the keys.
-__global__ __launch_bounds__(kThreads) void k_digit_totals(const uint32_t* __restrict__ keys, int64_t stride, int W,
-                                                           Passes passes, const uint32_t* __restrict__ n_dev,
+// Digit totals of every pass, in item order: one pass over the keys.  Every block
+// adds its counts to the same few thousand words, so few, large blocks: 128 to 256
+// of 1024 threads count 100000 items of 7 passes in 7 us, 400 of 256 in 9, 245000 of 5
+// in 9 and 12.5.
+constexpr int kTotalThreads = 1024;
+
+__global__ __launch_bounds__(kTotalThreads) void k_digit_totals(const uint32_t* __restrict__ keys, int64_t stride, int W,
+                                                           int passes, const uint32_t* __restrict__ n_dev,
                                                            uint32_t n_max, uint32_t* __restrict__ totals) {
   extern __shared__ uint32_t cnt[];   // [passes][kDigits]
   const uint32_t n = min(*n_dev, n_max);
   const int lane = threadIdx.x & (kWave - 1);
-  for (int i = threadIdx.x; i < passes.n * kDigits; i += kThreads) cnt[i] = 0;
+  for (int i = threadIdx.x; i < passes * kDigits; i += kTotalThreads) cnt[i] = 0;
   __syncthreads();
-  for (uint64_t i0 = (uint64_t)blockIdx.x * kThreads; i0 < n; i0 += (uint64_t)gridDim.x * kThreads) {
+  for (uint64_t i0 = (uint64_t)blockIdx.x * kTotalThreads; i0 < n; i0 += (uint64_t)gridDim.x * kTotalThreads) {
     const uint64_t i = i0 + threadIdx.x;
     const bool valid = i < n;
     int have = -1;
     uint32_t key = 0;
-    for (int p = 0; p < passes.n; ++p) {
-      const int bit = passes.bit(p);
+    for (int p = 0; p < passes; ++p) {
+      const int bit = 8 * p;
       if (bit / 32 != have) {
         have = bit / 32;
         key = valid ? keys[(W - 1 - have) * stride + i] : 0u;
@@ -189,7 +181,7 @@ __global__ __launch_bounds__(kThreads) void k_digit_totals(const uint32_t* __res
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < passes.n * kDigits; i += kThreads)
+  for (int i = threadIdx.x; i < passes * kDigits; i += kTotalThreads)
     if (cnt[i]) atomicAdd(&totals[i], cnt[i]);
 }
 
@@ -292,32 +284,31 @@ hipError_t ensure_scratch(dcem_ctx* c, int passes, int64_t n_max) {
 }  // namespace
 
 hipError_t prepare_sort(dcem_ctx* c, int bits, int64_t n_max) {
-  return ensure_scratch(c, Passes(bits, 32).n, n_max);
+  return ensure_scratch(c, (bits + 7) / 8, n_max);
 }
 
 hipError_t radix_sort_perm(dcem_ctx* c, const uint32_t* keys, int W, int bits, const uint32_t* n_dev,
-                           int64_t n_max, uint32_t* perm, uint32_t* perm_tmp, hipStream_t s, int64_t stride,
-                           int low_bits) {
+                           int64_t n_max, uint32_t* perm, uint32_t* perm_tmp, hipStream_t s, int64_t stride) {
   if (n_max <= 0) return hipSuccess;
   if (stride < 0) stride = n_max;
-  const Passes passes(bits, low_bits);
+  const int passes = (bits + 7) / 8;
   if (n_max <= kSmallSort) {
     hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(kSmallThreads), 0, s, keys, stride, W, passes, n_dev,
                        (uint32_t)n_max, perm);
     return hipGetLastError();
   }
   const int64_t tiles = sort_tiles(n_max);
-  hipError_t e = ensure_scratch(c, passes.n, n_max);
+  hipError_t e = ensure_scratch(c, passes, n_max);
   if (e != hipSuccess) return e;
-  const SortScratch sc(c->sort_hist.p, passes.n);
-  fill_u32(sc.totals, 0u, SortScratch::words(passes.n, tiles), s);
-  const unsigned blocks = (unsigned)std::min<int64_t>((n_max + kThreads - 1) / kThreads, 512);
-  hipLaunchKernelGGL(k_digit_totals, dim3(blocks), dim3(kThreads), sizeof(uint32_t) * kDigits * passes.n, s, keys,
+  const SortScratch sc(c->sort_hist.p, passes);
+  fill_u32(sc.totals, 0u, SortScratch::words(passes, tiles), s);
+  const unsigned blocks = (unsigned)std::min<int64_t>((n_max + kTotalThreads - 1) / kTotalThreads, 256);
+  hipLaunchKernelGGL(k_digit_totals, dim3(blocks), dim3(kTotalThreads), sizeof(uint32_t) * kDigits * passes, s, keys,
                      stride, W, passes, n_dev, (uint32_t)n_max, sc.totals);
   const uint32_t* src = nullptr;
-  for (int p = 0; p < passes.n; ++p) {
-    uint32_t* dst = (passes.n - 1 - p) % 2 == 0 ? perm : perm_tmp;
-    const int bit = passes.bit(p);
+  for (int p = 0; p < passes; ++p) {
+    uint32_t* dst = (passes - 1 - p) % 2 == 0 ? perm : perm_tmp;
+    const int bit = 8 * p;
     const auto pass = sort_rounds(n_max) == 4 ? k_sort_pass<4> : k_sort_pass<8>;
     hipLaunchKernelGGL(pass, dim3((unsigned)tiles), dim3(kThreads), 0, s, keys + (W - 1 - bit / 32) * stride, bit & 31,
                        src, dst, n_dev, (uint32_t)n_max, sc.totals + (size_t)p * kDigits, sc.ticket + p,
