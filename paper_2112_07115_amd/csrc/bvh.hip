@@ -81,13 +81,6 @@ __global__ void k_box_init(uint32_t* box, uint32_t n) {
   else if (threadIdx.x == 6) box[6] = n;
 }
 
-__global__ void k_set2(uint32_t* p, uint32_t a, uint32_t* q, uint32_t b) {
-  if (threadIdx.x == 0) {
-    *p = a;
-    *q = b;
-  }
-}
-
 // Bounds of the triangle centroids (exact min/max through order-preserving bits).
 __global__ void k_centroid_bounds(const float* __restrict__ V, const int32_t* __restrict__ T, int64_t nt,
                                   uint32_t* box) {
@@ -339,8 +332,13 @@ __global__ void k_karras(const uint32_t* __restrict__ key_hi, const uint32_t* __
                          Node* __restrict__ nodes, int32_t* __restrict__ leaf_parent,
                          int32_t* __restrict__ leaf_tri, int2* __restrict__ range,
                          const int32_t* __restrict__ tri_face, const int32_t* __restrict__ face_object,
-                         uint8_t* __restrict__ moves) {
+                         uint8_t* __restrict__ moves, uint32_t* __restrict__ refit_cnt,
+                         uint32_t* __restrict__ info, uint32_t* __restrict__ n_depth) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
+  // counters of the launches that follow (a launch for each would be 5 us)
+  if (i < n - 1) refit_cnt[i] = 0;
+  if (i < 3) info[2 + i] = 0;       // cross nodes, listed entries, finished blocks
+  if (i == 0) *n_depth = (uint32_t)(n - 1);
   bool moving = false;
   if (i < n) {
     leaf_tri[i] = (int32_t)perm[i];
@@ -735,9 +733,16 @@ hipError_t tree_from_keys(dcem_ctx* c, int key_words, int key_bits) {
   uint32_t* nbox = perm_tmp + nt;
   if ((e = radix_sort_perm(c, code, key_words, key_bits, nbox + 6, nt, perm, perm_tmp, c->stream)) != hipSuccess)
     return e;
-  fill_u32(ptr<uint32_t>(c->refit_cnt), 0u, (size_t)ni, c->stream);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  uint32_t* info = ptr<uint32_t>(c->tree_info);
+  uint32_t* dkey = ptr<uint32_t>(c->depth_key);
+  uint32_t* dperm = dkey + ni;
+  uint32_t* dtmp = dperm + ni;
+  uint32_t* dn = dtmp + ni;   // item count for the depth sort
   if (nt == 1) {
+    fill_u32(ptr<uint32_t>(c->refit_cnt), 0u, (size_t)ni, c->stream);
+    fill_u32(info + 2, 0u, 3, c->stream);
+    fill_u32(dn, (uint32_t)ni, 1, c->stream);
     Node root{};
     root.c = make_int4(~0, ~0, -1, 0);
     if ((e = hipMemcpyAsync(c->nodes.p, &root, sizeof(Node), hipMemcpyHostToDevice, c->stream)) != hipSuccess)
@@ -752,11 +757,9 @@ hipError_t tree_from_keys(dcem_ctx* c, int key_words, int key_bits) {
     hipLaunchKernelGGL(k_karras, dim3((nt + kKarrasBlock - 1) / kKarrasBlock), dim3(kKarrasBlock), 0, c->stream, key_hi,
                        key_lo, perm, (int)nt, ptr<Node>(c->nodes), ptr<int32_t>(c->leaf_parent),
                        ptr<int32_t>(c->leaf_tri), ptr<int2>(c->node_range), ptr<int32_t>(c->tri_face),
-                       ptr<int32_t>(c->face_object), ptr<uint8_t>(c->leaf_moves));
+                       ptr<int32_t>(c->face_object), ptr<uint8_t>(c->leaf_moves), ptr<uint32_t>(c->refit_cnt), info,
+                       dn);
   }
-  uint32_t* info = ptr<uint32_t>(c->tree_info);
-  hipLaunchKernelGGL(k_set2, dim3(1), dim3(64), 0, c->stream, info + 2, 0u, info + 3, 0u);
-  hipLaunchKernelGGL(k_set2, dim3(1), dim3(64), 0, c->stream, info + 4, 0u, info + 4, 0u);
   int32_t* cross = ptr<int32_t>(c->cross);
   hipLaunchKernelGGL(k_cross_mark, dim3((ni + 255) / 256), dim3(256), 0, c->stream, ptr<int2>(c->node_range), ni,
                      cross, cross + ni, info + 2);
@@ -765,12 +768,7 @@ hipError_t tree_from_keys(dcem_ctx* c, int key_words, int key_bits) {
                      ptr<uint32_t>(c->leaf_moves));
   launch_refit(c, false, c->sah_dev + 0);
   // 4-wide tree: binary nodes at even depth, breadth-first
-  uint32_t* dkey = ptr<uint32_t>(c->depth_key);
-  uint32_t* dperm = dkey + ni;
-  uint32_t* dtmp = dperm + ni;
-  uint32_t* dn = dtmp + ni;   // item count for the sort
   uint32_t* n4 = ptr<uint32_t>(c->tree_info);   // [0] = 4-wide node count
-  hipLaunchKernelGGL(k_set2, dim3(1), dim3(64), 0, c->stream, dn, (uint32_t)ni, dn, (uint32_t)ni);
   hipLaunchKernelGGL(k_depth_keys, dim3((ni + 255) / 256), dim3(256), 0, c->stream, ptr<Node>(c->nodes), ni, dkey);
   if ((e = radix_sort_perm(c, dkey, 1, 8, dn, ni, dperm, dtmp, c->stream)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_map4, dim3((ni + 255) / 256), dim3(256), 0, c->stream, dperm, dkey, ni,
