@@ -492,13 +492,14 @@ __device__ inline uint32_t slot_leaf_mask(const Node* __restrict__ nodes, int p)
 // its two children (boxes from c's slots).  Also stores the leaf-slot masks of
 // the node's child nodes (and the root's own mask in info[1]), the leaf
 // triangles in slot order and, per sorted leaf, its slot (where refits write
-// the moved triangle).
+// the moved triangle), and per triangle.
 __global__ void k_collapse(const Node* __restrict__ nodes, const float* __restrict__ V,
                            const int32_t* __restrict__ T, const int32_t* __restrict__ tri_face,
                            const int32_t* __restrict__ face_object, const int32_t* __restrict__ leaf_tri,
                            const int32_t* __restrict__ bvh2_of, const int32_t* __restrict__ map4,
                            uint32_t* __restrict__ info, Node4* __restrict__ out, Leaf* __restrict__ tri4,
-                           int32_t* __restrict__ leaf_slot, int32_t* __restrict__ slot4) {
+                           int32_t* __restrict__ leaf_slot, int32_t* __restrict__ tri_slot,
+                           int32_t* __restrict__ slot4) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= (int)info[0]) return;
   const int p = bvh2_of[q];
@@ -536,6 +537,7 @@ __global__ void k_collapse(const Node* __restrict__ nodes, const float* __restri
     if (ch[e] >= 0) continue;
     tri4[4 * (size_t)q + e] = leaf_record(V, T, tri_face, face_object, leaf_tri[~ch[e]]);
     leaf_slot[~ch[e]] = 4 * q + e;
+    tri_slot[leaf_tri[~ch[e]]] = 4 * q + e;
   }
   Node4 n;
   for (int e = 0; e < 4; ++e) {
@@ -567,12 +569,6 @@ void launch_xform(dcem_ctx* c, const float* xf) {
 
 // Build the binary LBVH and its 4-wide collapse, entirely on the stream (no
 // host round trip).  The SAH sum ratio of the new tree goes to sah_dev[0].
-__global__ void k_tri_slot(const int32_t* __restrict__ leaf_tri, const int32_t* __restrict__ leaf_slot, int n,
-                           int32_t* __restrict__ tri_slot) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) tri_slot[leaf_tri[i]] = leaf_slot[i];
-}
-
 __global__ void k_face_slots(const int32_t* __restrict__ face_tris, const int32_t* __restrict__ tri_slot, int n,
                              int32_t* __restrict__ face_slots) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -773,17 +769,13 @@ hipError_t tree_from_keys(dcem_ctx* c, int key_words, int key_bits) {
   if ((e = radix_sort_perm(c, dkey, 1, 8, dn, ni, dperm, dtmp, c->stream)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_map4, dim3((ni + 255) / 256), dim3(256), 0, c->stream, dperm, dkey, ni,
                      ptr<int32_t>(c->bvh2_of4), ptr<int32_t>(c->map4), n4);
+  if ((e = ensure(c->tri_slot, sizeof(int32_t) * nt)) != hipSuccess) return e;
   launch_collapse(c);
   // slot of every face triangle, for the refinement's face test (face_tris
   // lists every triangle once, grouped by face)
-  const int64_t nft = nt;
-  if ((e = ensure(c->tri_slot, sizeof(int32_t) * nt)) != hipSuccess) return e;
-  if ((e = ensure(c->face_slots, sizeof(int32_t) * std::max<int64_t>(nft, 1))) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_tri_slot, dim3((nt + 255) / 256), dim3(256), 0, c->stream, ptr<int32_t>(c->leaf_tri),
-                     ptr<int32_t>(c->leaf_slot), (int)nt, ptr<int32_t>(c->tri_slot));
-  if (nft > 0)
-    hipLaunchKernelGGL(k_face_slots, dim3((unsigned)((nft + 255) / 256)), dim3(256), 0, c->stream,
-                       ptr<int32_t>(c->face_tris), ptr<int32_t>(c->tri_slot), (int)nft, ptr<int32_t>(c->face_slots));
+  if ((e = ensure(c->face_slots, sizeof(int32_t) * nt)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_face_slots, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, c->stream,
+                     ptr<int32_t>(c->face_tris), ptr<int32_t>(c->tri_slot), (int)nt, ptr<int32_t>(c->face_slots));
   if ((e = hipGetLastError()) != hipSuccess) return e;
   c->has_bvh = true;
   return hipSuccess;
@@ -795,7 +787,8 @@ void launch_collapse(dcem_ctx* c) {
                      ptr<float>(c->vertices), ptr<int32_t>(c->tris), ptr<int32_t>(c->tri_face),
                      ptr<int32_t>(c->face_object), ptr<int32_t>(c->leaf_tri), ptr<int32_t>(c->bvh2_of4),
                      ptr<int32_t>(c->map4), ptr<uint32_t>(c->tree_info), ptr<Node4>(c->nodes4),
-                     ptr<Leaf>(c->tri4), ptr<int32_t>(c->leaf_slot), ptr<int32_t>(c->slot4));
+                     ptr<Leaf>(c->tri4), ptr<int32_t>(c->leaf_slot), ptr<int32_t>(c->tri_slot),
+                     ptr<int32_t>(c->slot4));
 }
 
 RefitArgs make_refit_args(dcem_ctx* c, bool wide, double* sah_out) {
