@@ -387,7 +387,7 @@ def roofline(stats, mode):
     kinds = [s["trace_kernel"] for s in sel]
     kind = max(set(kinds), key=kinds.count) if kinds else 0   # the traversal most frames used
     sel = [s for s in sel if s["trace_kernel"] == kind]
-    name = "k_trace_wave" if kind == 1 else "k_trace"
+    name = "k_trace_wave" if kind == 1 else "k_trace_packet"
     ms = float(np.mean([s["ms_trace"] for s in sel]))
     by = float(np.mean([trace_bytes(s, mode == "coherent") for s in sel]))
     segs = float(sum(s["segments"] for s in sel))

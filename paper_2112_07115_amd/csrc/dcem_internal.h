@@ -14,10 +14,8 @@ namespace dcem {
 constexpr int kWave = 64;
 constexpr float kTMin = 1e-4f;           // hits closer than this to a segment start are ignored
 constexpr double kTMinD = 1e-4;
-constexpr int kStackLds = 32;            // traversal stack entries of a thread of k_recapture kept in LDS
-constexpr int kStackSpill = 32;          // its further entries in device memory (rarely reached)
-constexpr int kStackSize = kStackLds + kStackSpill;
-constexpr int kTraceBlock = 128;         // threads per trace block
+constexpr int kStackSize = 64;           // traversal stack entries of a packet, and of a lane that walks by itself
+constexpr int kTraceBlock = 128;         // threads per block of a batched trace
 constexpr uint32_t kNoRay = 0xffffffffu;
 constexpr int32_t kTransmit = 1 << 30;   // decoded face entry: the interaction transmits through the face
 constexpr int32_t kFaceMask = kTransmit - 1;
@@ -238,7 +236,7 @@ struct dcem_ctx {
   dcem::DevBuf queues;       // chunk queues of the packet trace
   dcem::DevBuf count_part;   // item counts of each block of the last trace launch, added up by the reduction
   int count_blocks = 0;      // its blocks (0: the counters were added to directly)
-  dcem::DevBuf stack_spill;  // per-thread traversal stack entries beyond the LDS part (kStackSpill each)
+  dcem::DevBuf stack_spill;  // the lanes' traversal stack entries beyond those in LDS
   // One device block holding everything the host reads after a frame, copied
   // in one transfer to pinned host memory: counters (128 B), error word
   // (128 B), SAH values (256 B), then p_coh and p_inc.
@@ -371,7 +369,7 @@ int cu_count(dcem_ctx* c);   // compute units of the context's device
 void launch_fibonacci(dcem_ctx* c);
 // Trace all rays, or (coherent frame) the listed ones after keeping the
 // previous frame's still-valid captures.  Returns the traversal launched:
-// 0 one thread per ray, 1 one group of lanes per ray; -1 when its stack
+// 0 packets of rays, 1 one group of lanes per ray; -1 when its stack
 // space could not be allocated (nothing launched).
 int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, uint32_t n_prev_caps);
 void launch_coherence(dcem_ctx* c);
@@ -384,11 +382,11 @@ void launch_refit_coherence(dcem_ctx* c, bool begin, const uint32_t* skip = null
 // Clear the frame counters and seed the capture list with the LoS candidates.
 void launch_frame_begin(dcem_ctx* c, bool los, const uint32_t* skip = nullptr);
 hipError_t build_ray_order(dcem_ctx* c);
-// Buffers a frame's trace needs (the per-thread stack's spill space), sized
+// Buffers a frame's trace needs (the lanes' stacks' spill space), sized
 // before anything of the frame is enqueued.
 hipError_t prepare_trace(dcem_ctx* c);
 // Launch configuration of a batched trace (several contexts' full frames in
-// one persistent launch): per-thread stack entries kept in LDS, blocks per
+// one persistent launch): a lane's stack entries kept in LDS, blocks per
 // compute unit, work items per queue chunk.
 struct BatchShape {
   int lds_stack = 32;

@@ -248,8 +248,8 @@ struct TraceArgs {
   uint32_t* err;
   const Capture* prev_caps;   // coherent frames: the previous frame's captures to filter
   uint32_t n_prev;
-  int* stack_spill;           // [kStackSpill][grid threads] per-thread stack entries beyond the LDS part
-  int stack_thread;           // stack entries a per-thread traversal may use (<= kStackSize)
+  int* stack_spill;           // [entries][grid threads] the lanes' stack entries beyond those in LDS
+  int stack_thread;           // stack entries a packet or lane may use (<= kStackSize)
   uint32_t* count_part;       // [grid][3] item counts of each block (segments, nodes, triangle tests)
   int stack_group;            // stack entries a group traversal may use (<= kRayStack)
 };
@@ -1041,7 +1041,7 @@ __global__ __launch_bounds__(kTraceBlock, kPacketPerSimd) void k_trace_batch(con
 // id).  Entries whose distance exceeds the current best are skipped.  When a
 // group's stack empties it finishes the segment (logs, receivers, reflection)
 // and continues with the next segment or ray while the other groups keep
-// traversing.  Every triangle the per-thread traversal tests is tested here
+// traversing.  Every triangle the other traversals test is tested here
 // too (leaf triangles without their boxes, which only drops a conservative
 // filter), with the same arithmetic, so the hit is the same.
 // Lanes per ray: one DPP row.  (Measured on the re-trace of the urban
@@ -1809,10 +1809,6 @@ __global__ void k_dirs_by_pos(const float* __restrict__ dirs, const uint32_t* __
   out[3 * i] = d[0];
   out[3 * i + 1] = d[1];
   out[3 * i + 2] = d[2];
-}
-
-int trace_grid(dcem_ctx* c) {
-  return cu_count(c) * 8;   // 16 KB of LDS stack per block: eight blocks per CU
 }
 
 }  // namespace
