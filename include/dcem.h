@@ -468,7 +468,7 @@ dcem_status dcem_get_stats(dcem_ctx* ctx, dcem_frame_stats* out);
  * Each scene is a context holding its own scene, BVH and caches; a batch
  * traces one frame of every context (the frame algorithm of Sec. III per
  * scene, as dcem_trace_frame) with ONE persistent closest-hit launch for the
- * full traces of all of them: a queue of (scene, chunk of work items) that
+ * full traces of all of them: queues of (scene, chunk of work items) that
  * wavefronts drain, so scenes of very different sizes (ragged triangle
  * counts, transmitters, ray budgets, reflection limits, receivers, bands)
  * keep every compute unit busy to the end.  Contexts in coherent mode trace
@@ -514,7 +514,7 @@ dcem_status dcem_batch_trace(dcem_batch* batch, const dcem_trace_params* params)
 
 /* Autotuner of the batched trace: traces the batch's frame `repeats` times for
  * each candidate shape (LDS stack 32 with 4, 6 or 8 blocks per compute unit,
- * LDS stack 16 with 4 to 16 blocks, chunk 256; then chunks 64 and 1024 at the
+ * LDS stack 16 with 4 to 16 blocks, chunk 64; then chunks 128 and 256 at the
  * best of those), times the batched launch with HIP events, and keeps the
  * fastest shape.  The contexts hold the last traced frame (equal to every
  * other one).  Synchronises. */

@@ -1739,12 +1739,12 @@ dcem_status dcem_batch_trace(dcem_batch* b, const dcem_trace_params* params) {
 dcem_status dcem_batch_tune(dcem_batch* b, const dcem_trace_params* params, int32_t repeats) {
   if (!b) return DCEM_E_INVALID_ARG;
   if (!params || repeats < 1) return batch_fail(b, DCEM_E_INVALID_ARG, "null params or repeats < 1");
-  // block shape and LDS stack depth first (chunk 256), then the chunk
+  // block shape and LDS stack depth first (chunk 64), then the chunk
   std::vector<dcem::BatchShape> cand;
   for (int lds : {32, 16})
     for (int bpc : {4, 6, 8, 12, 16}) {
       if (lds == 32 && bpc > 8) continue;   // 16 KB of LDS stack per block: at most 9 blocks per CU
-      cand.push_back(dcem::BatchShape{lds, bpc, 256});
+      cand.push_back(dcem::BatchShape{lds, bpc, 64});
     }
   auto time_shape = [&](const dcem::BatchShape& sh, float* best_ms) -> dcem_status {
     float sum = 0.f;
@@ -1771,7 +1771,7 @@ dcem_status dcem_batch_tune(dcem_batch* b, const dcem_trace_params* params, int3
       best_shape = sh;
     }
   }
-  for (int chunk : {64, 1024}) {
+  for (int chunk : {128, 256}) {
     dcem::BatchShape sh = best_shape;
     sh.chunk = chunk;
     float ms = 0.f;

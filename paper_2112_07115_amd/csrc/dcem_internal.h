@@ -391,7 +391,7 @@ hipError_t prepare_trace(dcem_ctx* c);
 struct BatchShape {
   int lds_stack = 32;
   int blocks_per_cu = 8;
-  int chunk = 256;
+  int chunk = 64;
 };
 // Bytes of spill space a batched trace of this shape needs.
 size_t batch_spill_bytes(const dcem_ctx* c, const BatchShape& shape);

@@ -659,7 +659,7 @@ struct CaptureStage {
 // SIMD overlap.  Trace times against one ray per lane (us): urban scene, 2^20
 // rays 531 -> 342; 256 sources of 4096 rays 1006 -> 800; indoor office
 // with transmission, 2^18 rays per branch 1210 -> 722; eight cities of up to
-// 2^20 rays in one launch 3500 (with looser trees) -> 2004;
+// 2^20 rays in one launch 3500 (with looser trees) -> 1158;
 // toy scene, 4096 rays in packets of 4 81 -> 40; a list of re-traced rays of
 // the highway scene 1405 -> 904.
 template <bool kList>
@@ -988,46 +988,52 @@ __global__ __launch_bounds__(kRecapBlock) void k_recapture(TraceArgs a) {
 // Full traces of several scenes in one persistent launch.  args[j] describes
 // scene j's frame (all rays, no work list); its items are cut into chunks of
 // `chunk` consecutive work items, chunk_start[j] the first chunk of scene j in
-// one queue over all scenes (chunk_start[n] the total).  A wavefront takes the
-// next chunk, finds its scene and traces the chunk's items in packets; counts
-// and errors go to that scene's frame.  A lane's stack keeps its first S entries
-// in LDS.
+// one sequence over all scenes (chunk_start[n] the total), shared out by
+// ChunkQueues.  A wavefront takes the next chunk, finds its scene and traces the
+// chunk's items in packets; counts, captures and errors go to that scene's frame
+// when the wavefront leaves it.  A lane's stack keeps its first S entries in LDS.
+// Eight cities of up to 2^20 rays, chunks of 64, 128, 256 and 512 items: 1158,
+// 1372, 1909 and 2931 us (large ones leave a launch waiting at its end); off one
+// queue, with the counts added after each chunk, 2295, 1624, 1987 and 3109.
 template <int S>
 __global__ __launch_bounds__(kTraceBlock, kPacketPerSimd) void k_trace_batch(const TraceArgs* __restrict__ args,
                                                              const uint32_t* __restrict__ chunk_start, int n_scene,
-                                                             uint32_t chunk, uint32_t* __restrict__ queue,
+                                                             uint32_t chunk, uint32_t* __restrict__ queues,
                                                              int* __restrict__ spill) {
   __shared__ int stack_mem[S * kTraceBlock];
   __shared__ Capture cap_mem[kTraceBlock / kWave][kPacketCaps];
-  const int lane = threadIdx.x & (kWave - 1);
-  const uint32_t total = chunk_start[n_scene];
-  while (true) {
-    uint32_t g = 0;
-    if (lane == 0) g = atomicAdd(queue, 1u);
-    g = __builtin_amdgcn_readfirstlane(g);   // uniform: the scene's arguments load as scalars
-    if (g >= total) break;
+  CaptureStage stage{cap_mem[threadIdx.x / kWave]};
+  ItemCounts ic;
+  int scene = -1;   // of the counts and captures not yet added
+  auto leave_scene = [&]() {
+    if (scene < 0) return;
+    stage.flush(args[scene], ic.cap_over);
+    flush_counts(args[scene], ic);
+  };
+  ChunkQueues src(queues, chunk_start[n_scene]);
+  uint32_t g;
+  while (src.chunk(g)) {   // uniform: the scene's arguments load as scalars
     int lo = 0, hi = n_scene - 1;   // the last scene whose first chunk is <= g
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (chunk_start[mid] <= g) lo = mid; else hi = mid - 1;
     }
+    if (lo != scene) leave_scene();
+    scene = lo;
     const TraceArgs a = args[lo];
     ThreadStack stack{stack_mem + threadIdx.x, spill + blockIdx.x * (size_t)kTraceBlock + threadIdx.x,
                       (size_t)gridDim.x * kTraceBlock, a.stack_thread, S, kTraceBlock};
     const int n4 = a.n4_dev ? (int)*a.n4_dev : 0;
     const uint32_t base = (g - chunk_start[lo]) * chunk;
     const uint32_t end = min(base + chunk, (uint32_t)a.n_work);
-    ItemCounts ic;
-    CaptureStage stage{cap_mem[threadIdx.x / kWave]};
     for (uint32_t w = base; w < end;) {
       const uint32_t vsrc = w / (uint32_t)a.n_rays, p0 = w - vsrc * (uint32_t)a.n_rays;
       const uint32_t p1 = min(min(p0 + (uint32_t)kWave, p0 + (end - w)), (uint32_t)a.n_rays);
       trace_packet<false>(a, vsrc, p0, p1, n4, stage, stack, ic);
       w += p1 - p0;
     }
-    stage.flush(a, ic.cap_over);
-    flush_counts(a, ic);
   }
+  leave_scene();
 }
 
 // Group-per-ray tracing for short work lists (the rays a coherent frame
@@ -1925,7 +1931,7 @@ int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, 
 }
 
 size_t batch_table_bytes(int n) {
-  return ((sizeof(TraceArgs) * (size_t)n + 255) / 256) * 256 + sizeof(uint32_t) * ((size_t)n + 1) + 256;
+  return ((sizeof(TraceArgs) * (size_t)n + 255) / 256) * 256 + sizeof(uint32_t) * ((size_t)n + 1 + kXcds * kQueueStride);
 }
 
 size_t batch_spill_bytes(const dcem_ctx* c, const BatchShape& shape) {
@@ -1951,10 +1957,10 @@ hipError_t launch_trace_batch(dcem_ctx* const* cs, const uint8_t* keep_cache, in
   }
   hc[n] = (uint32_t)total;
   if (total >= (uint64_t)1 << 32) return hipErrorInvalidValue;
-  uint32_t* queue = reinterpret_cast<uint32_t*>(static_cast<char*>(table.p) + args_bytes + sizeof(uint32_t) * (n + 1));
+  uint32_t* queues = reinterpret_cast<uint32_t*>(static_cast<char*>(table.p) + args_bytes + sizeof(uint32_t) * (n + 1));
   hipError_t e = hipMemcpyAsync(table.p, host_table, args_bytes + sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return e;
-  fill_u32(queue, 0u, 1, s);
+  fill_u32(queues, 0u, kXcds * kQueueStride, s);
   const TraceArgs* dargs = static_cast<const TraceArgs*>(table.p);
   const uint32_t* dchunk = reinterpret_cast<const uint32_t*>(static_cast<char*>(table.p) + args_bytes);
   const int want = (int)std::min<uint64_t>((total * shape.chunk + kTraceBlock - 1) / kTraceBlock + 1,
@@ -1963,10 +1969,10 @@ hipError_t launch_trace_batch(dcem_ctx* const* cs, const uint8_t* keep_cache, in
   int* sp = ptr<int>(spill);
   if (shape.lds_stack == 16)
     hipLaunchKernelGGL(k_trace_batch<16>, dim3(grid), dim3(kTraceBlock), 0, s, dargs, dchunk, n,
-                       (uint32_t)shape.chunk, queue, sp);
+                       (uint32_t)shape.chunk, queues, sp);
   else if (shape.lds_stack == 32)
     hipLaunchKernelGGL(k_trace_batch<32>, dim3(grid), dim3(kTraceBlock), 0, s, dargs, dchunk, n,
-                       (uint32_t)shape.chunk, queue, sp);
+                       (uint32_t)shape.chunk, queues, sp);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -22,3 +22,29 @@ def test_spread(n, graph, own_stream):
     stream = torch.cuda.Stream() if own_stream else None
     run_batched_and_single(ws, range(4), graph=graph and own_stream, modes=modes,
                            stream=stream.cuda_stream if own_stream else None)
+
+
+@pytest.mark.parametrize("shape", [(16, 1, 64), (32, 8, 64), (32, 32, 64), (16, 16, 128), (32, 4, 1 << 20)])
+def test_shapes(shape):
+    """Chunks shared out by the per-XCD queues: fewer chunks than wavefronts and
+    many more, more blocks than are resident, chunks of several packets and of
+    whole scenes; paths, powers and the counts added per scene."""
+    ws = small_batch(5, seed=71, budget_range=(1 << 10, 1 << 16))
+    bctx, sctx = [[dcem.Context(0) for _ in ws] for _ in range(2)]
+    for c, d, s in zip(bctx, sctx, ws):
+        c.scene_upload(s)
+        d.scene_upload(s)
+    batch = dcem.Batch(bctx)
+    batch.set_shape(*shape)
+    for _ in range(2):
+        batch.trace([dcem.scene_frame_args(s) for s in ws])
+        for c, d, s in zip(bctx, sctx, ws):
+            d.trace_frame(**dcem.scene_frame_args(s))
+            got, want = [x.received_power() + tuple(v for _, v in sorted(x.paths().items())) for x in (c, d)]
+            for a, b in zip(got, want):
+                assert np.array_equal(a, b)
+            for k in ("segments", "captures", "rays_traced"):
+                assert c.stats()[k] == d.stats()[k], k
+    batch.close()
+    for c in bctx + sctx:
+        c.close()
