@@ -1057,7 +1057,7 @@ constexpr int kGroups = kWave / kRayLanes;  // rays per wavefront
 constexpr int kRayStack = kRayLanes == 64 ? 256 : kGroupStack;   // stack entries per ray
 constexpr int kWaveRx = 512;                // receivers cached in LDS (more are read from memory)
 constexpr int kCapStage = 256;              // new captures a block stages in LDS
-constexpr int64_t kWaveTraceMax = 1 << 16;  // longest list traced by groups
+constexpr int64_t kWaveTraceMax = 1 << 16;  // longest list traced by groups (160000 rays: 1330 us, in packets 898)
 
 __device__ inline bool hit_less(float ta, int ia, float tb, int ib) { return ta < tb || (ta == tb && ia < ib); }
 
@@ -1910,8 +1910,9 @@ int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, 
   }
   // packets of 64 rays, or of fewer while that leaves the chip idle: 4096 rays
   // take 75 us in packets of 64 and 40 us in packets of 4, 65536 rays 129 us at
-  // 8, 16 or 32 wavefronts per compute unit (a list may turn out a quarter
-  // longer than the last frame's)
+  // 8, 16 or 32 wavefronts per compute unit; the 160000 listed rays of the highway
+  // scene 1003, 898, 934 and 1054 in packets of 64, 32, 16 and 8 (a list may turn out
+  // a quarter longer than the last frame's)
   const int64_t n = all_rays ? c->n_rays : expected + expected / 4 + 1;
   const int64_t lists = all_rays ? (int64_t)c->n_src * c->n_branch : 1;
   const int64_t cu = cu_count(c);
