@@ -233,6 +233,7 @@ struct dcem_ctx {
   dcem::DevBuf caps[2];      // double-buffered capture lists
   int cur_caps = 0;
   dcem::DevBuf work_list, invalid_flag;   // re-trace list; per-ray first invalid segment (255 = valid)
+  dcem::DevBuf chunk_order;  // packets of 64 positions in the order the trace starts them
   dcem::DevBuf queues;       // chunk queues of the packet trace
   dcem::DevBuf count_part;   // item counts of each block of the last trace launch, added up by the reduction
   int count_blocks = 0;      // its blocks (0: the counters were added to directly)
@@ -300,7 +301,7 @@ struct dcem_ctx {
             &nodes, &leaf_slot, &leaf_tri, &leaf_parent, &refit_cnt, &morton, &sort_tmp, &sah_part, &scene_box,
             &node_range, &nodes4, &bvh2_of4, &map4, &depth_key, &slot4, &cross, &tree_info, &leaf_moves, &tri4, &face_build,
             &dirs, &dirs_by_pos, &ray_order, &src_pos, &tgt_pos, &freqs, &rx_nodes, &rx_cols, &grad_buf, &face_log, &ray_state,
-            &seg_o, &seg_d, &log_tri, &log_t, &log_len, &caps[0], &caps[1], &work_list, &invalid_flag, &stack_spill, &queues, &count_part,
+            &seg_o, &seg_d, &log_tri, &log_t, &log_len, &caps[0], &caps[1], &work_list, &invalid_flag, &stack_spill, &chunk_order, &queues, &count_part,
             &frame_block, &cand_keys, &cand_perm, &cand_tmp, &uniq_idx, &first_ray, &path_valid, &path_len,
             &path_tau, &path_aod, &path_aoa, &path_amp, &pair_range, &path_order, &path_faces, &path_pts,
             &sort_hist, &series_buf, &expand_buf, &face_pen, &mat_pen, &branch_set};
