@@ -221,7 +221,7 @@ struct TraceArgs {
   int n_work;
   int n_src;
   uint32_t packet;            // rays per packet
-  const uint32_t* chunk_order; // the order in which a source's packets of 64 start (null: by position)
+  const uint32_t* chunk_order; // the order in which the one source's packets of 64 start (null: by position)
   const uint32_t* work_list;  // null: all work items
   int K;                      // interactions at most (segments 0..K)
   // Transmission (the "Reflected and transmitted rays" item of Sec. III):
@@ -867,9 +867,8 @@ __global__ __launch_bounds__(kPacketBlock, kPacketPerSimd) void k_trace_packet(T
     uint32_t vsrc = 0, p = i;
     if (!kList) {
       if (a.chunk_order) {
-        const uint32_t n_vsrc = (uint32_t)(a.n_src * a.n_branch);
-        const uint32_t c = src.interleaved(i), rank = c / n_vsrc;
-        vsrc = c - rank * n_vsrc;
+        const uint32_t c = src.interleaved(i), rank = c / (uint32_t)a.n_branch;
+        vsrc = c - rank * (uint32_t)a.n_branch;
         p = __builtin_amdgcn_readfirstlane(a.chunk_order[rank]);
       } else {
         vsrc = i / per_src;
@@ -1944,10 +1943,16 @@ int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, 
   const int64_t cu = cu_count(c);
   a.packet = kWave;
   while (a.packet > kMinPacket && lists * ((n + a.packet - 1) / a.packet) < cu * kPacketWaves) a.packet /= 2;
-  // Packets of 64 start level ones first, and all sources' packets of one direction
-  // together (build_ray_order).  Smaller ones have no order made: they are taken where
-  // the launch has fewer packets than wavefronts, so all start at once.
-  if (all_rays && a.packet == kWave) a.chunk_order = ptr<uint32_t>(c->chunk_order);
+  // One source's packets of 64 start level ones first, its branches' packets of one
+  // direction together (build_ray_order).  Several sources' start by position: an
+  // XCD's part is then one source's rays in one sector, which its L2 holds more of
+  // the tree for (2^20 rays of each of 4 sources over 273k, 606k and 2.04 million
+  // triangles of the highway scene: frames 3.12, 3.15 and 4.00 ms by position, 3.25,
+  // 3.29 and 4.11 in the order; cities of 30k to 2 million 0 to 6 % the other way).
+  // One source gains at every size measured: the cities of 30k and 115k 0.56 -> 0.49
+  // and 0.93 -> 0.86 ms, the highway's 2^22 rays 4.12 -> 4.00.  Smaller packets are
+  // taken where there are no more of them than wavefronts: all start at once.
+  if (all_rays && a.packet == kWave && c->n_src == 1) a.chunk_order = ptr<uint32_t>(c->chunk_order);
   const int64_t want = (lists * ((n + a.packet - 1) / a.packet) * kWave + kPacketBlock - 1) / kPacketBlock;
   const int grid = (int)std::max<int64_t>(16, std::min<int64_t>(cu * kPacketPerSimd, want));
   if (prepare_trace(c) != hipSuccess) {   // sized already by the frame's setup
@@ -2105,9 +2110,9 @@ void launch_refit_coherence(dcem_ctx* c, bool begin, const uint32_t* skip) {
 // from the horizontal, in 64 steps.  A full launch is a few packets per wavefront,
 // so it ends when the last long packet does.  Level rays of a scene wider than
 // high meet most and leave last, steep ones hit the ground or the sky: started
-// first, the long ones are covered by the short.  By position 346 us (262144 rays
-// in the urban scene) and 722 us (3 sources in the office), in this order 319 and
-// 632.
+// first, the long ones are covered by the short.  By position 346 us (2^20 rays
+// in the urban scene) and 722 us (2^18 rays by 11 transmission branches in the
+// office), in this order 319 and 632.
 __global__ void k_chunk_keys(const float* __restrict__ dirs_by_pos, uint32_t n_chunks, uint32_t* __restrict__ key,
                              uint32_t* __restrict__ count) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;

@@ -1,6 +1,7 @@
-"""GPU: packets of 64 rays are started in an order of their own: several sources,
-ray counts with remainders, and chunk counts that the eight queues do not share
-evenly, each source's captures against the oracle."""
+"""GPU: one source's packets of 64 rays start in an order of their own, several
+sources' by position: ray counts with remainders and packet counts that the eight
+queues do not share evenly, with and without transmission branches, against the
+oracle."""
 import numpy as np
 import pytest
 
@@ -17,9 +18,9 @@ def O():
     return oracle
 
 
-# just above 4096 packets in all: an order sorted by one workgroup and by several,
-# a last packet of 1 ray, 5 rays and 64, directions along the vertical axis only
-@pytest.mark.parametrize("n_src,n", [(3, 64 * 1366 + 1), (41, 64 * 103 + 5), (7, 64 * 600)])
+# just above 4096 packets in all; a last packet of 1 ray, 5 rays and 64; directions
+# along the vertical axis only, whose packets all have one key
+@pytest.mark.parametrize("n_src,n", [(1, 64 * 4096), (1, 64 * 4102 + 1), (1, 64 * 8193 + 5), (3, 64 * 1366 + 1), (41, 64 * 103 + 5), (7, 64 * 600)])
 @pytest.mark.parametrize("vertical", [False, True])
 def test_sources(O, n_src, n, vertical):
     s = scenes.static_toy()
@@ -31,5 +32,18 @@ def test_sources(O, n_src, n, vertical):
     ctx = dcem.Context(0)
     log("sources", n_src, "rays", n, "vertical", vertical)
     st, out, ofr = run_pair(ctx, O, s, dirs=dirs, n_rays=None if vertical else n)
+    assert_comparable(st)
+    ctx.close()
+
+
+# 11 branches of one source: the shortest order that is used, a last packet of 7 rays,
+# and one that gives the queues a remainder of 3 packets
+@pytest.mark.parametrize("n", [64 * 372 + 7, 64 * 384 + 1])
+def test_branches(O, n):
+    s = scenes.indoor_office(n_rays=n)
+    assert s.tx.shape[0] == 1
+    ctx = dcem.Context(0)
+    log("branches", n)
+    st, out, ofr = run_pair(ctx, O, s, n_rays=n)
     assert_comparable(st)
     ctx.close()
