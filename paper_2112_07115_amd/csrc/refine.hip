@@ -1118,7 +1118,10 @@ __global__ __launch_bounds__(256) void k_series_items(const int32_t* __restrict_
   for (int d = 1; d <= kMaxK; ++d) {
     run_min[d - 1] = kNoRay;
     if (d > S.K) continue;   // uniform
-    eq = eq && __shfl_up(fld[d - 1], 1) == fld[d - 1];
+    // every lane takes part in the shuffle (a lane left out would be read as 0,
+    // the field of a reflection on face 0)
+    const uint32_t pfld = __shfl_up(fld[d - 1], 1);
+    eq = eq && pfld == fld[d - 1];
     const bool has = d >= d0 && d <= depth;
     const bool same = has && eq && d >= pd0 && d <= pdepth;
     // runs: each starts at an item that does not continue its predecessor's
@@ -1260,7 +1263,8 @@ __global__ __launch_bounds__(256) void k_face_boxes(const int32_t* __restrict__ 
   // a face's triangles are consecutive: each run of one face in the
   // wavefront is reduced first and enters the face's box with one set of
   // atomics (a face of many triangles would otherwise serialise on them)
-  const bool head = ok && (lane == 0 || __shfl_up(f, 1) != f);
+  const int pf = __shfl_up(f, 1);   // by every lane
+  const bool head = ok && (lane == 0 || pf != f);
   const uint64_t starts = __ballot(!ok || head);
   const uint64_t above = lane == kWave - 1 ? 0ull : starts & ~((2ull << lane) - 1ull);
   const int last = above ? __ffsll((unsigned long long)above) - 2 : kWave - 1;
