@@ -1023,6 +1023,9 @@ dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan
 // Device part of a frame up to the trace: the frame's start (counters, line
 // of sight records), the pending refit, the revalidation pass.
 dcem_status frame_front(dcem_ctx* c, const FramePlan& plan) {
+  // no trace of this frame has left counts yet (its own launch sets the number of
+  // blocks; a batched trace, or none where there are no rays, leaves it at 0)
+  c->count_blocks = 0;
   if (!plan.ahead) {
     ev_record(c, 0);
     if (!c->frame_begun) c->cur_caps ^= 1;
@@ -1051,7 +1054,6 @@ dcem_status frame_front(dcem_ctx* c, const FramePlan& plan) {
 dcem_status frame_trace(dcem_ctx* c, const FramePlan& plan) {
   ev_record(c, 8);
   if (plan.recapture && plan.n_work > 0) launch_recapture(c);
-  c->count_blocks = 0;
   const int traversal =
       plan.n_work > 0 ? launch_trace(c, !plan.coherent, plan.keep_cache, plan.expected, plan.n_prev) : 0;
   if (traversal < 0) return fail(c, DCEM_E_OUT_OF_MEMORY, "alloc traversal stack");
@@ -1610,7 +1612,6 @@ dcem_status batch_frame(dcem_batch* b, const dcem_trace_params* params, const dc
     if (e != hipSuccess) st = hip_fail(c, e, "batched trace");
     for (dcem_ctx* f : full) {
       f->last_trace_kernel = 0;
-      f->count_blocks = 0;   // added to the counters by the batched trace
       ev_record(f, 2);
     }
   }
