@@ -264,9 +264,10 @@ const char* dcem_last_error(const dcem_ctx* ctx);
  * DCEM_ERR_CAPTURES. */
 dcem_status dcem_set_capture_capacity(dcem_ctx* ctx, int64_t max_captures);
 /* Cap the closest-hit traversal stacks at `entries` entries per query (0
- * restores the full depth: 64 per packet, and per ray of a packet that has
- * lost its coherence, 128 in the group traversal; larger values are clamped to those).  Results do not
- * change unless a stack overflows; an overflow drops the entries that do not
+ * restores the full depth: 64 per packet and per ray by itself, 128 in the
+ * group traversal; larger values are clamped to those).  A packet whose stack
+ * is full goes on ray by ray.  Results do not
+ * change unless a ray's own stack overflows; an overflow drops the entries that do not
  * fit, sets DCEM_ERR_STACK, and is reported as DCEM_E_CAPACITY by the next
  * synchronising call (that frame's outputs are undefined).  The full depth
  * holds every tree this library builds; smaller caps exercise the overflow
