@@ -648,6 +648,8 @@ dcem_status dcem_scene_upload(dcem_ctx* c, const dcem_scene_desc* s) {
   c->nv = s->n_vertices;
   c->nt = s->n_tris;
   c->nf = nf;
+  c->most_face_tris = 1;
+  for (int f = 0; f < nf; ++f) c->most_face_tris = std::max<int64_t>(c->most_face_tris, off[f + 1] - off[f]);
   c->nm = s->n_materials;
   c->mat_pending = false;
   // every material opaque until dcem_set_penetration_loss says otherwise

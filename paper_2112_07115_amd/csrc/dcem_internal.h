@@ -165,6 +165,7 @@ struct dcem_ctx {
   bool has_scene = false;
   int64_t nv = 0, nt = 0;
   int32_t nf = 0, nm = 0, no = 0;
+  int64_t most_face_tris = 1;   // triangles of the face that has most
   float pad = 0.f;          // absolute padding of leaf boxes (conservative traversal)
   dcem::DevBuf ref_vertices, vertices, tris, tri_face, face_material, face_object, materials,
       obj_range, face_tri_off, face_tris, face_ref_tri, xf, obj_box, face_plane;
