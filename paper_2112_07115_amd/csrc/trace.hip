@@ -189,7 +189,7 @@ constexpr int kWaves = 4;                   // wavefronts per block of the group
 constexpr int kWaveBlock = kWaves * kWave;
 constexpr int kPacketBlock = 256;            // threads per block of k_trace_packet
 constexpr int kPacketPerSimd = 4;            // its wavefronts per SIMD, and so blocks per compute unit
-constexpr int kPacketStack = 16;             // per-lane traversal stack entries in LDS (16 KB)
+constexpr int kPacketStack = 32;             // per-lane traversal stack entries in LDS (32 KB; all that four blocks leave)
 constexpr int kMinPacket = 4, kPacketWaves = 16;   // smallest packet; wavefronts per compute unit it keeps
 constexpr uint32_t kPacketTrial = 16, kPacketNum = 5, kPacketDen = 10;   // see incoherent()
 struct TraceArgs {
@@ -253,6 +253,7 @@ struct TraceArgs {
   int stack_thread;           // stack entries a packet or lane may use for a closest hit (<= kStackSize)
   uint32_t* count_part;       // [grid][3] item counts of each block (segments, nodes, triangle tests)
   int stack_group;            // stack entries a group traversal may use (<= kRayStack)
+  int rx_stack;               // stack entries of a walk of the capture spheres' tree (k_recapture)
 };
 
 // Coherent frames: keep each capture of the previous frame made before its
@@ -350,12 +351,11 @@ __device__ inline void add_capture(const TraceArgs& a, uint32_t work, uint32_t t
 // Captures of one segment [o, o + tend d] (tend infinite on a miss; th its
 // hit distance): capture spheres whose padded box the segment meets, by their
 // 4-wide tree, then the exact closest-approach test, and add(sphere).  The tree
-// is built by halves, so its walk holds at most 3 entries for each of its at most
-// 14 levels (2^27 spheres): the full stack, whatever limit closest-hit traversals
-// are given.
+// is built by halves, so its walk holds at most rx_stack_entries() entries, 39 for
+// 2^27 spheres: they fit in `room`, whatever limit closest-hit traversals are given.
 template <class Add>
 __device__ __forceinline__ void capture_walk(const TraceArgs& a, const Ray& r, float tend, float dd, ThreadStack& stack,
-                                             bool& overflow, Add add) {
+                                             int room, bool& overflow, Add add) {
   int node = 0, sp = 0;
   for (int guard = a.n_rx_nodes + 2; guard > 0; --guard) {
     const Node4 nd = node_in_memory(a.rx_nodes, node);
@@ -371,7 +371,7 @@ __device__ __forceinline__ void capture_walk(const TraceArgs& a, const Ray& r, f
         if (captured(r, tend, dd, a.rx[3 * c], a.rx[3 * c + 1], a.rx[3 * c + 2], a.r2)) add(c);
       } else if (next < 0) {
         next = ch;
-      } else if (sp < kStackSize) {
+      } else if (sp < room) {
         stack.put(sp++, ch);
       } else {
         overflow = true;
@@ -389,7 +389,7 @@ __device__ void capture_segment(const TraceArgs& a, const Ray& r, bool hit, floa
                                 uint32_t work, uint32_t txi, int k, ThreadStack& stack, bool& overflow,
                                 bool& cap_over) {
   if (!a.capture || !in_rx_band(a, r, hit, th)) return;
-  capture_walk(a, r, tend, dd, stack, overflow, [&](int c) { add_capture(a, work, txi, c, k, cap_over); });
+  capture_walk(a, r, tend, dd, stack, kStackSize, overflow, [&](int c) { add_capture(a, work, txi, c, k, cap_over); });
 }
 
 // xy bounds [x0, x1] x [y0, y1] of the centres of the capture spheres that the
@@ -973,7 +973,7 @@ __global__ __launch_bounds__(kRecapBlock) void k_recapture(TraceArgs a) {
       const float tend = segment(w, (int)q.y, r);
       setup_ray(r);
       const uint32_t txi = vsrc / (uint32_t)a.n_branch;
-      capture_walk(a, r, tend, dot_dd(r), stack, overflow, [&](int c) {
+      capture_walk(a, r, tend, dot_dd(r), stack, a.rx_stack, overflow, [&](int c) {
         const uint32_t at = atomicAdd(&n_caps[wave], 1u);
         if (at < kRecapCaps) caps[wave][at] = Capture{w, ((txi * (uint32_t)a.n_rx + (uint32_t)c) << 4) | q.y};
         else add_capture(a, w, txi, c, (int)q.y, cap_over);
@@ -1862,6 +1862,14 @@ void launch_fibonacci(dcem_ctx* c) {
 // blocks drain a shared queue).
 namespace {
 
+// Stack entries a walk of the tree over n capture spheres needs: three at each level
+// above the last (a node covers a quarter of its parent's spheres, rounded up).
+int rx_stack_entries(int64_t n) {
+  int entries = 0;
+  for (; n > 4; n = (n + 3) / 4) entries += 3;
+  return entries;
+}
+
 // Arguments of a context's trace launch.
 TraceArgs trace_args(dcem_ctx* c, bool all_rays, bool keep_cache, uint32_t n_prev_caps) {
   const int64_t n_work = (int64_t)c->n_src * c->n_branch * c->n_rays;
@@ -1927,6 +1935,7 @@ TraceArgs trace_args(dcem_ctx* c, bool all_rays, bool keep_cache, uint32_t n_pre
   a.stack_spill = nullptr;
   a.stack_thread = c->stack_limit > 0 ? std::min(c->stack_limit, kStackSize) : kStackSize;
   a.stack_group = c->stack_limit > 0 ? std::min(c->stack_limit, kRayStack) : kRayStack;
+  a.rx_stack = std::max(rx_stack_entries(c->n_tgt), kRecapStack);
   return a;
 }
 
@@ -2040,7 +2049,9 @@ hipError_t prepare_trace(dcem_ctx* c) {
   if (e != hipSuccess) return e;
   const size_t packet =
       (size_t)(kStackSize - kPacketStack) * kPacketBlock * (size_t)std::max(cu_count(c) * kPacketPerSimd, 16);
-  const size_t recapture = (size_t)(kStackSize - kRecapStack) * kRecapBlock * (size_t)cu_count(c) * kRecapPerCu;
+  // (the spheres' tree spills beyond 4096 of them only)
+  const size_t recapture = (size_t)std::max(rx_stack_entries(c->n_tgt) - kRecapStack, 0) * kRecapBlock *
+                           (size_t)cu_count(c) * kRecapPerCu;
   return ensure(c->stack_spill, sizeof(int) * std::max(packet, recapture));
 }
 
