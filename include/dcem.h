@@ -473,7 +473,9 @@ dcem_status dcem_get_stats(dcem_ctx* ctx, dcem_frame_stats* out);
  * wavefronts drain, so scenes of very different sizes (ragged triangle
  * counts, transmitters, ray budgets, reflection limits, receivers, bands)
  * keep every compute unit busy to the end.  Contexts in coherent mode trace
- * their own (short) re-trace lists.  Results are per context, read with
+ * their own (short) re-trace lists, and contexts of several sources (or
+ * branches) with fewer than 64 rays each their own launch.  Results are per
+ * context, read with
  * dcem_received_power / dcem_get_* on each, and equal those of
  * dcem_trace_frame bitwise. */
 typedef struct dcem_batch dcem_batch;

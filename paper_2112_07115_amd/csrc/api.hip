@@ -1579,7 +1579,8 @@ dcem_status spread_contexts(dcem_batch* b, const std::vector<FramePlan>& plan, P
 
 // One batched frame: every context's host part, then the device work of all
 // of them (frame starts and refits, the full traces in one persistent launch
-// (coherent contexts trace their own re-trace lists), candidates, refinement,
+// (coherent contexts trace their own re-trace lists, and those of few rays per
+// source their own rays), candidates, refinement,
 // reductions and read-backs), captured as one HIP graph when asked for and
 // possible.  `timed`: HIP events around the batched trace (direct launch).
 dcem_status batch_frame(dcem_batch* b, const dcem_trace_params* params, const dcem::BatchShape& shape, bool timed) {
@@ -1593,11 +1594,13 @@ dcem_status batch_frame(dcem_batch* b, const dcem_trace_params* params, const dc
   HIP_TRY(hipSetDevice(b->device), "set device");
   if (batch_buffers(b, shape) != hipSuccess) return batch_fail(b, DCEM_E_OUT_OF_MEMORY, "alloc batch buffers");
   std::vector<dcem_ctx*> full;
+  std::vector<uint8_t> own(n, 0);    // traced by a launch of its own, in its part
   std::vector<uint8_t> full_cache;   // the full trace stores the segment cache (a coherent frame follows)
   bool capturable = b->use_graph && b->stream != nullptr && !timed;
   for (int j = 0; j < n; ++j) {
     dcem_ctx* cj = b->ctx[j];
-    if (!plan[j].coherent && plan[j].n_work > 0) {
+    own[j] = plan[j].coherent || (plan[j].n_work > 0 && few_rays(cj));
+    if (!own[j] && plan[j].n_work > 0) {
       full.push_back(cj);
       full_cache.push_back(plan[j].keep_cache ? 1 : 0);
     }
@@ -1620,7 +1623,7 @@ dcem_status batch_frame(dcem_batch* b, const dcem_trace_params* params, const dc
   if (st == DCEM_OK && timed) (void)hipEventRecord(b->ev[1], b->stream);
   if (st == DCEM_OK)
     st = spread_contexts(b, plan, [&](int j) {
-      const dcem_status ts = plan[j].coherent ? frame_trace(b->ctx[j], plan[j]) : DCEM_OK;
+      const dcem_status ts = own[j] ? frame_trace(b->ctx[j], plan[j]) : DCEM_OK;
       return ts == DCEM_OK ? frame_back(b->ctx[j], plan[j]) : ts;
     });
   if (capturable) {

@@ -374,6 +374,9 @@ void launch_fibonacci(dcem_ctx* c);
 // 0 packets of rays, 1 one group of lanes per ray; -1 when its stack
 // space could not be allocated (nothing launched).
 int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, uint32_t n_prev_caps);
+// Does a full trace of the context's rays mix its sources (a launch of its own,
+// also in a batch)?
+bool few_rays(const dcem_ctx* c);
 void launch_coherence(dcem_ctx* c);
 // Coherent frame with moved receivers: captures of the kept segments of every
 // cached ray against the current receivers (after the revalidation pass).

@@ -667,7 +667,8 @@ struct CaptureStage {
 // best hit, so the result does not depend on the tree), captures, reflections,
 // the per-bounce face log and segment cache.  The rays are the positions
 // [p0, p1) of source and branch vsrc or, with kList, the work list's items
-// [p0, p1), each from its restart segment.
+// [p0, p1), each from its restart segment; without a list the work items
+// [p0, p1) of any sources, each ray by itself.
 //
 // Consecutive positions are rays of neighbouring directions, and planar faces
 // keep them together: on the urban scene with 2^20 rays a packet enters 10 to
@@ -691,7 +692,7 @@ __device__ __forceinline__ void trace_packet(const TraceArgs& a, uint32_t vsrc, 
   uint32_t pos = live ? p0 + lane : p0;
   uint32_t work;
   if constexpr (kList) {
-    work = a.work_list[pos];
+    work = a.work_list ? a.work_list[pos] : pos;
     vsrc = work / (uint32_t)a.n_rays;
     pos = work - vsrc * (uint32_t)a.n_rays;
   } else {
@@ -703,7 +704,7 @@ __device__ __forceinline__ void trace_packet(const TraceArgs& a, uint32_t vsrc, 
   const uint32_t tset = a.n_branch > 1 ? a.branch_set[vsrc - txi * (uint32_t)a.n_branch] : 0u;
   const int last_t = tset ? 31 - __builtin_clz(tset) : -1;
   const uint32_t rid = a.log_tri ? vsrc * (uint32_t)a.n_rays + a.ray_order[pos] : 0u;
-  const int k0 = kList ? (int)a.restart[work] : 0;
+  const int k0 = kList && a.restart ? (int)a.restart[work] : 0;
   Ray r;
   float L = 0.0f;
   int excl = -1, ended = 0;   // ended: segments of the ray once it has ended
@@ -719,7 +720,8 @@ __device__ __forceinline__ void trace_packet(const TraceArgs& a, uint32_t vsrc, 
     excl = a.face_log[(size_t)(k0 - 1) * a.n_work + work];
   }
   setup_ray(r);
-  bool together = true;   // the rays walk the tree as a packet
+  // the rays walk the tree as a packet (not those of several sources)
+  bool together = !kList || a.work_list;
   for (int s = 0; s <= a.K; ++s) {
     const int k = k0 + s;   // the segment (of a live ray at most K)
     const int n_live = __popcll(__ballot(live));
@@ -867,8 +869,8 @@ __global__ __launch_bounds__(kPacketBlock, kPacketPerSimd) void k_trace_packet(T
   const int n4 = a.n4_dev ? (int)*a.n4_dev : 0;
   CaptureStage stage{cap_mem[threadIdx.x / kWave]};
   ItemCounts ic;
-  const uint32_t n_pos = kList ? a.counters[kCntList] : (uint32_t)a.n_rays;
-  if (kList && blockIdx.x == 0 && threadIdx.x == 0) a.counters[kCntWork] = n_pos;
+  const uint32_t n_pos = !kList ? (uint32_t)a.n_rays : a.work_list ? a.counters[kCntList] : (uint32_t)a.n_work;
+  if (kList && a.work_list && blockIdx.x == 0 && threadIdx.x == 0) a.counters[kCntWork] = n_pos;
   const uint32_t per_src = (n_pos + a.packet - 1) / a.packet;   // chunks
   ChunkQueues src(a.queues, kList ? per_src : per_src * (uint32_t)(a.n_src * a.n_branch));
   uint32_t i;
@@ -1941,6 +1943,14 @@ TraceArgs trace_args(dcem_ctx* c, bool all_rays, bool keep_cache, uint32_t n_pre
 
 }  // namespace
 
+// Sources (or branches) of fewer rays than a wavefront has lanes: a full trace
+// takes 64 work items of any of them together, each ray by itself, as packets of one
+// source would leave lanes idle and so few rays to all sides share little of the
+// tree anyway.  Urban scene, K = 4, in packets and mixed: 65536 sources of 1, 4 and 16 rays
+// 271 and 122, 1391 and 260, 2492 and 968 us; 16384 of 24, 48 and 64 rays 747 and 436,
+// 886 and 736, 975 and 928; 4096 of 256 rays 951 and 903.
+bool few_rays(const dcem_ctx* c) { return c->n_rays < kWave && (int64_t)c->n_src * c->n_branch > 1; }
+
 int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, uint32_t n_prev_caps) {
   TraceArgs a = trace_args(c, all_rays, keep_cache, n_prev_caps);
   if (!all_rays && expected <= kWaveTraceMax && c->n_branch == 1) {
@@ -1956,8 +1966,9 @@ int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, 
   // 8, 16 or 32 wavefronts per compute unit; the 160000 listed rays of the highway
   // scene 1003, 898, 934 and 1054 in packets of 64, 32, 16 and 8 (a list may turn out
   // a quarter longer than the last frame's)
-  const int64_t n = all_rays ? c->n_rays : expected + expected / 4 + 1;
-  const int64_t lists = all_rays ? (int64_t)c->n_src * c->n_branch : 1;
+  const bool mixed = all_rays && few_rays(c);
+  const int64_t n = mixed ? a.n_work : all_rays ? c->n_rays : expected + expected / 4 + 1;
+  const int64_t lists = all_rays && !mixed ? (int64_t)c->n_src * c->n_branch : 1;
   const int64_t cu = cu_count(c);
   a.packet = kWave;
   while (a.packet > kMinPacket && lists * ((n + a.packet - 1) / a.packet) < cu * kPacketWaves) a.packet /= 2;
@@ -1979,7 +1990,7 @@ int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, 
   }
   a.stack_spill = ptr<int>(c->stack_spill);
   c->count_blocks = grid;
-  if (all_rays) hipLaunchKernelGGL(k_trace_packet<false>, dim3(grid), dim3(kPacketBlock), 0, c->stream, a);
+  if (all_rays && !mixed) hipLaunchKernelGGL(k_trace_packet<false>, dim3(grid), dim3(kPacketBlock), 0, c->stream, a);
   else hipLaunchKernelGGL(k_trace_packet<true>, dim3(grid), dim3(kPacketBlock), 0, c->stream, a);
   return 0;
 }
