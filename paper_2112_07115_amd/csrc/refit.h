@@ -43,10 +43,14 @@ struct RefitArgs {
 };
 
 // Trees with more leaves than this finish their cross nodes in a launch of
-// their own (one block; cross nodes beyond the LDS capacity climb through
-// device memory with workgroup-scope arrivals) instead of in the refit's last
-// block, which would otherwise fall back to device-scope arrivals.
-constexpr int64_t kCrossKernelLeaves = 512 * 1024;
+// their own: in one block's LDS when they fit, else climbed in device memory by
+// the threads of several blocks, with device-scope arrivals.  A tree has about ten
+// cross nodes for each refit block of 1024 leaves, so LDS (kMaxCross) ends a little
+// above this.  Below, the refit's last block finishes them 8 us sooner; above, that
+// block could not, and every block would count its arrivals at them in device memory,
+// still leaves included: 116k, 192k, 287k and 460k leaves 103, 154, 249 and 423 us
+// with the line at 512k, 62, 67, 93 and 111 now.
+constexpr int64_t kCrossKernelLeaves = 96 * 1024;
 
 // Arguments of a refit of the current tree (`wide`: also the 4-wide tree in
 // place), its SAH ratio written to sah_out.
@@ -316,10 +320,12 @@ __device__ __forceinline__ void refit_tail(const RefitArgs& a, int n_rb, bool ld
 // it computes every face's plane (used by the refinement's image method).
 // A block none of whose leaves can move (args.moves) keeps its boxes, planes and
 // area sum from the build or an earlier refit and only takes part in the count
-// of finished blocks: on the highway scene, 200 vehicles among 2 million
-// triangles, the launch shared with the revalidation takes 633 us for 937 and the
-// cross nodes' 355 for 484; a city of 120000 triangles 39 us for 42, the urban scene
-// of 32 blocks, bound by the chain of levels, 31 for 33.
+// of finished blocks (where cross slots are not listed, in a tree of unusually many
+// cross nodes below kCrossKernelLeaves, every block is refitted): on the highway
+// scene, 200 vehicles among 2 million triangles, the launch shared with the
+// revalidation takes 633 us for 937 and the cross nodes' 355 for 484; a city of 94000
+// triangles 35 us for 42, the urban scene of 32 blocks, bound by the chain of
+// levels, 31 for 33.
 // rb and n_rb: this block's index among the refit blocks and their number (the
 // refit may share a launch with other work).
 __device__ __forceinline__ void refit_block(const RefitArgs& a, int rb, int n_rb) {
