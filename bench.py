@@ -340,8 +340,10 @@ def cpu_baseline(scene):
 # Algorithmic bytes of one closest-hit launch (what the traversal must read
 # and write, counted once per use; nothing assumed cached):
 #   packet kernel: 128 B per 4-wide node a packet or a ray by itself fetches,
-#     48 B per ray-triangle test, per ray 13 B (direction, order entry, state), per segment 4 B (face log)
-#     + 32 B when the segment cache is kept, 8 B per capture record;
+#     per ray 13 B (direction, order entry, state), per segment 4 B (face log)
+#     + 32 B when the segment cache is kept, 8 B per capture record (triangles
+#     are left out: a packet reads one once for all its rays, and the count is
+#     of the rays' tests);
 #   group kernel: per node visit its four 32-byte slots (a leaf slot reads its
 #     48-byte triangle instead: +16 B per triangle test), per ray 42 B (list
 #     entry, restart, cached segment, face, state), per segment 84 B (face log,
@@ -350,7 +352,7 @@ def trace_bytes(s, kernel_cache):
     if s["trace_kernel"] == 1:
         return 128 * s["nodes_visited"] + 16 * s["tri_tests"] + 42 * s["rays_traced"] + 84 * s["segments"] \
             + 8 * s["captures"]
-    return 128 * s["nodes_visited"] + 48 * s["tri_tests"] + 13 * s["rays_traced"] \
+    return 128 * s["nodes_visited"] + 13 * s["rays_traced"] \
         + (4 + (32 if kernel_cache else 0)) * s["segments"] + 8 * s["captures"]
 
 
