@@ -314,8 +314,8 @@ dcem_status dcem_set_object_transforms(dcem_ctx* ctx, const float* xf, int32_t n
  * test asks for put the static geometry and every moving object in subtrees of
  * their own, and inside them mostly every face, so that refits under rigid
  * motion keep the tree tight; a
- * forced rebuild orders all triangles along one Morton curve, the better tree
- * for a frame traced without refitting.  Rebuilding never changes traced
+ * forced rebuild orders all triangles along one Morton curve, the shorter
+ * build (closest hits on its tree take between 6 % less and 21 % more time).  Rebuilding never changes traced
  * results: hits are the lexicographic minimum of (distance, triangle id) over
  * conservative boxes. */
 dcem_status dcem_refit_bvh(dcem_ctx* ctx, int32_t flags, double rebuild_threshold,

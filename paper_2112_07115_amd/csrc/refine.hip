@@ -130,7 +130,7 @@ __global__ void k_keys(const Capture* __restrict__ caps, const uint32_t* __restr
 // the decoded candidate (see UniqueOut).  The set of keys, their order and
 // the lowest ray per key equal those of a stable sort of all captures
 // followed by run heads.
-// As many captures as the workgroup's LDS takes (137 KB; a list expected to
+// As many captures as the workgroup's LDS takes (116 KB; a list expected to
 // fill three quarters of it goes the long way): 2200 captures take 22 us, the key,
 // sort, head and record launches of a longer list 60.
 constexpr int kSmallN = 3072;

@@ -1954,7 +1954,7 @@ bool few_rays(const dcem_ctx* c) { return c->n_rays < kWave && (int64_t)c->n_src
 int launch_trace(dcem_ctx* c, bool all_rays, bool keep_cache, int64_t expected, uint32_t n_prev_caps) {
   TraceArgs a = trace_args(c, all_rays, keep_cache, n_prev_caps);
   if (!all_rays && expected <= kWaveTraceMax && c->n_branch == 1) {
-    // short re-trace list: one wavefront per ray
+    // short re-trace list: a group of 16 lanes per ray, four rays per wavefront
     const int64_t want = (expected + expected / 4 + kWaves * kGroups - 1) / (kWaves * kGroups) + 1;
     const int grid = (int)std::max<int64_t>(16, std::min<int64_t>((int64_t)cu_count(c) * 8, want));
     c->count_blocks = grid;
