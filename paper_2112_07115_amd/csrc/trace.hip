@@ -678,11 +678,11 @@ struct CaptureStage {
 // Bound by vector issue (box tests, and triangle tests in dense scenes) and by
 // the round trips of a packet's dependent node loads, which four wavefronts per
 // SIMD overlap.  Trace times against one ray per lane (us): urban scene, 2^20
-// rays 531 -> 342; 256 sources of 4096 rays 1006 -> 800; indoor office
-// with transmission, 2^18 rays per branch 1210 -> 722; eight cities of up to
+// rays 531 -> 342 (315 in the packet order); 256 sources of 4096 rays 1006 -> 785; indoor
+// office with transmission, 2^18 rays per branch 1210 -> 722 (622); eight cities of up to
 // 2^20 rays in one launch 3500 (with looser trees) -> 1158;
 // toy scene, 4096 rays in packets of 4 81 -> 40; a list of re-traced rays of
-// the highway scene 1405 -> 904.
+// the highway scene 1405 -> 907.
 template <bool kList>
 __device__ __forceinline__ void trace_packet(const TraceArgs& a, uint32_t vsrc, uint32_t p0, uint32_t p1, int n4,
                                              CaptureStage& stage, ThreadStack& stack, ItemCounts& ic) {
