@@ -49,14 +49,18 @@ def test_each_source_alone(n_src, n, backward):
 
 
 @pytest.mark.parametrize("n", [3, 63])
-def test_cache_and_batch(n):
+@pytest.mark.parametrize("graph", [False, True])
+def test_cache_and_batch(n, graph):
+    import torch
     s = scenes.dynamic_urban()
     tx = np.asarray(s.tx, np.float32)[:1] + np.float32([[2 * j, j % 3, 0] for j in range(40)])
     s = scenes.Scene(**{**s.__dict__, "tx": tx, "n_rays": n, "rx_radius": 4.0})
-    coh, full, b0, b1 = ctxs = [dcem.Context(0) for _ in range(4)]
+    stream = torch.cuda.Stream()
+    coh, full, b0, b1 = ctxs = [dcem.Context(0, stream=stream.cuda_stream) for _ in range(4)]
     for c in ctxs:
         c.scene_upload(s)
     batch = dcem.Batch([b0, b1])
+    batch.set_graph(graph)
     for frame in range(4):
         for c in ctxs:
             c.set_object_transforms(s.transforms(frame))
@@ -71,6 +75,7 @@ def test_cache_and_batch(n):
         for k in ("segments", "captures", "rays_traced"):
             assert b1.stats()[k] == full.stats()[k]
     assert coh.stats()["coherent"] == 1 and coh.stats()["rays_traced"] < 40 * n
+    assert batch.info()["graph_frames"] >= (3 if graph else 0)
     batch.close()
     for c in ctxs:
         c.close()
