@@ -308,11 +308,20 @@ hipError_t ensure_frame_block(dcem_ctx* c, int64_t n_pow) {
       return e;
     if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
   }
-  e = ensure(c->frame_block, bytes);
-  if (e != hipSuccess) return e;
+  // both halves of the new block before the old ones go: a refit or rebuild writes
+  // into the block whether a frame follows or not
+  DevBuf block;
+  block.al = c->frame_block.al;
+  void* host = nullptr;
+  if ((e = ensure(block, bytes)) != hipSuccess) return e;
+  if ((e = hipHostMalloc(&host, block.bytes, hipHostMallocDefault)) != hipSuccess) {
+    release(block);
+    return e;
+  }
+  release(c->frame_block);
   if (c->host_block) (void)hipHostFree(c->host_block);
-  c->host_block = nullptr;
-  if ((e = hipHostMalloc(&c->host_block, c->frame_block.bytes, hipHostMallocDefault)) != hipSuccess) return e;
+  c->frame_block = block;
+  c->host_block = host;
   c->host_block_bytes = c->frame_block.bytes;
   char* b = ptr<char>(c->frame_block);
   c->cnt_dev = reinterpret_cast<uint32_t*>(b);
@@ -910,8 +919,14 @@ dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan
   const bool coherent = p->mode == DCEM_MODE_COHERENT && c->cache_valid && same_geom;
   const bool keep_cache = p->keep_cache != 0 || p->mode == DCEM_MODE_COHERENT;
   plan.recapture = coherent && rx_moved && !visited;   // visited series are tried against the current targets
+  // From here on the context describes the new frame.  Until that frame is
+  // enqueued (frame_done) there is none: a call that fails on the way leaves
+  // neither results to be read by the new sizes, nor a cache to be revalidated by
+  // them, nor inputs taken for uploaded.
+  const bool had_frame = c->has_frame;
+  c->has_frame = c->cache_valid = false;
   // -- device inputs
-  const bool need_dirs = !same_geom || !c->has_frame;
+  const bool need_dirs = !same_geom || !had_frame;
   const bool need_rx = need_dirs || rx_moved;
   cfg.n_src = n_src;
   cfg.n_tgt = n_tgt;
@@ -1007,14 +1022,14 @@ dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan
   // moved receivers: captures taken again; visited series: no captures
   plan.n_prev = (plan.recapture || visited) ? 0u : (uint32_t)c->n_caps_host;
   plan.n_work = n_work;
-  plan.expected = coherent ? ((c->has_frame && c->stats.coherent) ? (int64_t)c->last_cnt[kCntWork] : n_work) : n_work;
-  plan.small = !visited && c->has_frame && same_geom && c->n_caps_host <= small_path_capacity() * 3 / 4 &&
+  plan.expected = coherent ? ((had_frame && c->stats.coherent) ? (int64_t)c->last_cnt[kCntWork] : n_work) : n_work;
+  plan.small = !visited && had_frame && same_geom && c->n_caps_host <= small_path_capacity() * 3 / 4 &&
                small_path_fits(c);
   plan.visited = visited;
   // more captures than the one workgroup holds: the sort-based path, sized
   // from the last frame's count with room to grow, so the frame needs no
   // host round trip (a larger count is redone exactly when read)
-  if (!plan.small && !visited && c->has_frame && same_geom)
+  if (!plan.small && !visited && had_frame && same_geom)
     plan.hint = std::min<int64_t>(c->cap_capacity, 2 * c->n_caps_host + 4096);
   plan.coherent = coherent;
   plan.keep_cache = keep_cache;

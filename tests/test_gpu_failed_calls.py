@@ -1,0 +1,101 @@
+"""GPU: a frame whose buffers cannot be allocated (an allocator that says so at the k-th
+request, for every k) is reported as out of memory and leaves no frame: results are refused
+until one is traced, refits and trees go on, and the same call then gives what a fresh
+context gives, coherent frames after it too."""
+import numpy as np
+import pytest
+
+from paper_2112_07115_amd import dcem, scenes
+
+pytestmark = pytest.mark.gpu
+
+
+class Failing:
+    """torch's allocator, failing every request after `left` more (None: never)."""
+
+    def __init__(self):
+        base = dcem.TorchAllocator(0)
+        self.left, self.refused = None, 0
+
+        def alloc(n, stream, user):
+            if self.left is not None:
+                if self.left == 0:
+                    self.refused += 1
+                    return None
+                self.left -= 1
+            return base._alloc(n, stream, user)
+
+        self._alloc, self._base = dcem._ALLOC_FN(alloc), base
+        self.desc = dcem.AllocatorDesc(self._alloc, base._free, None)
+
+
+def outputs(c):
+    return c.received_power() + tuple(v for _, v in sorted(c.paths().items())) + c.trace_log()
+
+
+def refused(c):
+    for read in (c.received_power, c.paths, c.trace_log, c.stats, c.captures, c.power_gradients):
+        with pytest.raises(dcem.DcemError) as e:
+            read()
+        assert e.value.status == dcem.E_STATE
+
+
+@pytest.mark.parametrize("how", ["frame", "visited", "batch"])
+def test_frame(how):
+    s = scenes.box_field(40, 3, half=60.0, n_rays=500)
+    rx = np.asarray(s.rx, np.float32)
+    small = dict(tx=s.tx, rx=rx[:5], rx_radius=1.0, n_rays=500, max_reflections=1, freqs_hz=[28e9], record_trace_log=True,
+                 mode=dcem.MODE_COHERENT)
+    big = dict(tx=s.tx, rx=rx, rx_radius=2.0, n_rays=20_000, max_reflections=4, freqs_hz=[28e9, 60e9, 3e9],
+               record_trace_log=True, mode=dcem.MODE_COHERENT,
+               discovery=dcem.DISCOVER_VISITED if how == "visited" else 0)
+
+    def move(c, frame):
+        c.set_object_transforms(s.transforms(frame))
+        c.refit_bvh(threshold=float("inf"))
+
+    ref = dcem.Context(0)
+    ref.scene_upload(s)
+    want = []
+    for frame in (1, 2):
+        move(ref, frame)
+        ref.trace_frame(**big)
+        want.append(outputs(ref))
+    k, done = 0, False
+    while not done:
+        al = Failing()
+        c, other = dcem.Context(0, allocator=al), dcem.Context(0)
+        batch = dcem.Batch([other, c]) if how == "batch" else None
+        for x in (c, other):
+            x.scene_upload(s)
+            move(x, 0)
+            x.trace_frame(**small)
+            x.received_power()
+            move(x, 1)
+        al.left = k
+        try:
+            batch.trace([big, big]) if batch else c.trace_frame(**big)
+            done = al.refused == 0
+            assert done
+        except dcem.DcemError as e:
+            assert e.status == dcem.E_OUT_OF_MEMORY
+            for x in (c, other) if batch else (c,):
+                refused(x)
+                move(x, 1)
+                x.vertices(), x.bvh()
+        al.left = None
+        for f, frame in enumerate((1, 2)):
+            if f:
+                move(c, frame), move(other, frame)
+            if f or not done:
+                batch.trace([big, big]) if batch else c.trace_frame(**big)
+            for x in (c, other) if batch else (c,):
+                for a, b in zip(outputs(x), want[f]):
+                    assert np.array_equal(a, b, equal_nan=True)
+        assert c.stats()["coherent"] == 1
+        k += 1
+        if batch:
+            batch.close()
+        c.close(), other.close()
+    print(how, "allocations", k - 1, flush=True)
+    assert k > 10
