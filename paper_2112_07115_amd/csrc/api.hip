@@ -577,10 +577,6 @@ dcem_status dcem_scene_upload(dcem_ctx* c, const dcem_scene_desc* s) {
       (s->n_objects && !s->object_vertex_range))
     return fail(c, DCEM_E_INVALID_ARG, "null array with nonzero size");
   HIP_TRY(hipSetDevice(c->device), "set device");
-  c->refit_pending = false;   // the new scene is built from scratch
-  c->frame_begun = false;
-  c->revalidated_ahead = false;
-  c->early_ahead = false;
   std::vector<float> V;
   std::vector<int32_t> T, TF, FM, FO;
   std::vector<double> M;
@@ -661,6 +657,13 @@ dcem_status dcem_scene_upload(dcem_ctx* c, const dcem_scene_desc* s) {
     if (ref[f] < 0) return fail(c, DCEM_E_INVALID_ARG, "face %d has no triangle", f);
     if (!(best[f] > 0.0)) return fail(c, DCEM_E_INVALID_ARG, "face %d has only degenerate triangles", f);
   }
+  // the arguments are sound: from here on the old scene is gone, and until the new
+  // one's tree is built there is none
+  c->has_scene = c->has_frame = c->cache_valid = false;
+  c->refit_pending = false;   // the new scene is built from scratch
+  c->frame_begun = false;
+  c->revalidated_ahead = false;
+  c->early_ahead = false;
   c->still_faces = still_faces;
   c->nv = s->n_vertices;
   c->nt = s->n_tris;
@@ -696,8 +699,6 @@ dcem_status dcem_scene_upload(dcem_ctx* c, const dcem_scene_desc* s) {
   HIP_TRY(hipGetLastError(), "transform kernel");
   HIP_TRY(build_lbvh(c, true), "build BVH");
   c->has_scene = true;
-  c->cache_valid = false;
-  c->has_frame = false;
   c->bvh_stale = false;
   c->sah_last = 1.0;
   c->last_rebuilt = 1;
@@ -762,6 +763,7 @@ dcem_status dcem_refit_bvh(dcem_ctx* c, int32_t flags, double threshold, int32_t
       if (st != DCEM_OK) return st;
     }
     c->refit_pending = false;
+    c->bvh_stale = true;   // (until the rebuild is enqueued)
     ev_record(c, 6);
     // a forced rebuild serves the frame at hand; one the quality test asks
     // for keeps the objects apart for the refits that follow

@@ -99,3 +99,67 @@ def test_frame(how):
         c.close(), other.close()
     print(how, "allocations", k - 1, flush=True)
     assert k > 10
+
+
+def test_upload():
+    """No scene is left by an upload that cannot allocate; the next one starts anew."""
+    small, big = scenes.box_field(5, 2, n_rays=500), scenes.box_field(300, 20, n_rays=4000)
+    args = dcem.scene_frame_args(big, record_trace_log=True)
+    ref = dcem.Context(0)
+    ref.scene_upload(big)
+    ref.trace_frame(**args)
+    want = outputs(ref)
+    k, done = 0, False
+    while not done:
+        al = Failing()
+        c = dcem.Context(0, allocator=al)
+        c.scene_upload(small)
+        c.trace_frame(**dcem.scene_frame_args(small, record_trace_log=True))
+        c.received_power()
+        al.left = k
+        try:
+            c.scene_upload(big)
+            done = al.refused == 0
+            assert done
+        except dcem.DcemError as e:
+            assert e.status == dcem.E_OUT_OF_MEMORY
+            refused(c)
+            for call in (lambda: c.trace_frame(**args), c.refit_bvh, c.vertices, c.bvh,
+                         lambda: c.set_object_transforms(big.transforms(1))):
+                with pytest.raises(dcem.DcemError) as e2:
+                    call()
+                assert e2.value.status == dcem.E_STATE
+        al.left = None
+        if not done:
+            c.scene_upload(big)
+        c.trace_frame(**args)
+        for a, b in zip(outputs(c), want):
+            assert np.array_equal(a, b, equal_nan=True)
+        c.close()
+        k += 1
+    print("upload allocations", k - 1, flush=True)
+    assert k > 10
+
+
+def test_refused_upload_keeps_the_scene():
+    """An upload with bad arguments changes nothing, a refit still to run included."""
+    s = scenes.box_field(40, 3, half=60.0, n_rays=4000)
+    bad = scenes.Scene(**{**s.__dict__, "tris": np.where(s.tris == 5, 10**6, s.tris).astype(np.int32)})
+    got = []
+    for upload in (False, True):
+        c = dcem.Context(0)
+        c.scene_upload(s)
+        c.trace_frame(**dcem.scene_frame_args(s))
+        c.received_power()
+        c.set_object_transforms(s.transforms(3))
+        c.refit_bvh(threshold=float("inf"))
+        if upload:
+            with pytest.raises(dcem.DcemError) as e:
+                c.scene_upload(bad)
+            assert e.value.status == dcem.E_INVALID_ARG
+        _, box, _ = c.bvh()
+        c.trace_frame(**dcem.scene_frame_args(s, record_trace_log=True))
+        got.append((box,) + outputs(c))
+        c.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b, equal_nan=True)
