@@ -280,7 +280,8 @@ dcem_status dcem_set_timing(dcem_ctx* ctx, int32_t enabled);
 /* Copy the scene to the device and build its LBVH (paper Sec. III: the BVH
  * over the environment's triangles).  Replaces any previous scene and drops
  * the ray cache.  Validates indices and finiteness on the host (host inputs)
- * and returns DCEM_E_INVALID_ARG on a violation. */
+ * and returns DCEM_E_INVALID_ARG on a violation, the previous scene unchanged.
+ * After any other error there is no scene (calls return DCEM_E_STATE). */
 dcem_status dcem_scene_upload(dcem_ctx* ctx, const dcem_scene_desc* scene);
 
 /* Place the moving objects for the next frame (paper Sec. III: objects move
@@ -321,7 +322,10 @@ dcem_status dcem_set_object_transforms(dcem_ctx* ctx, const float* xf, int32_t n
 dcem_status dcem_refit_bvh(dcem_ctx* ctx, int32_t flags, double rebuild_threshold,
                            int32_t* rebuilt, double* sah_ratio);
 
-/* Trace one frame (asynchronous on the context stream). */
+/* Trace one frame (asynchronous on the context stream).  Bad arguments change
+ * nothing.  After any other error (out of memory, too many visited series; in
+ * a batch also for the contexts set up before the one that failed) the context
+ * has no frame and no ray cache: reading results returns DCEM_E_STATE. */
 dcem_status dcem_trace_frame(dcem_ctx* ctx, const dcem_trace_params* params);
 
 /* Received power of the last frame, [n_freqs][n_tx][n_rx] FP64 watts:
