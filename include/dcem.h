@@ -323,9 +323,10 @@ dcem_status dcem_refit_bvh(dcem_ctx* ctx, int32_t flags, double rebuild_threshol
                            int32_t* rebuilt, double* sah_ratio);
 
 /* Trace one frame (asynchronous on the context stream).  Bad arguments change
- * nothing.  After any other error (out of memory, too many visited series; in
- * a batch also for the contexts set up before the one that failed) the context
- * has no frame and no ray cache: reading results returns DCEM_E_STATE. */
+ * nothing, in a batch of no context.  After any other error (out of memory, too
+ * many visited series; in a batch also for the contexts set up before the one that
+ * failed) the context has no frame and no ray cache: reading results returns
+ * DCEM_E_STATE. */
 dcem_status dcem_trace_frame(dcem_ctx* ctx, const dcem_trace_params* params);
 
 /* Received power of the last frame, [n_freqs][n_tx][n_rx] FP64 watts:

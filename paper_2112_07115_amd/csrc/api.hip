@@ -835,10 +835,8 @@ struct FramePlan {
   uint32_t n_prev = 0;      // captures of the previous frame (kept by a coherent frame)
 };
 
-// Host part of a frame: argument checks, the unread previous frame, the
-// configuration, uploads and buffers.  Enqueues nothing of the frame itself
-// beyond the uploads (and, when the rays changed, their directions and order).
-dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan) {
+// The argument checks of a frame; nothing is changed but the error text.
+dcem_status frame_check(dcem_ctx* c, const dcem_trace_params* p) {
   if (!c) return DCEM_E_INVALID_ARG;
   c->err.clear();
   if (!c->has_scene) return fail(c, DCEM_E_STATE, "no scene uploaded");
@@ -859,17 +857,14 @@ dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan
   if (p->trace_from_rx != 0 && p->trace_from_rx != 1) return fail(c, DCEM_E_INVALID_ARG, "trace_from_rx must be 0 or 1");
   if (p->discovery != DCEM_DISCOVER_CAPTURE && p->discovery != DCEM_DISCOVER_VISITED)
     return fail(c, DCEM_E_INVALID_ARG, "bad discovery mode");
-  const bool visited = p->discovery == DCEM_DISCOVER_VISITED;
   if (p->max_transmissions < 0 || p->max_transmissions > DCEM_MAX_TRANSMISSIONS)
     return fail(c, DCEM_E_INVALID_ARG, "max_transmissions must be in [0, %d]", DCEM_MAX_TRANSMISSIONS);
   if (p->max_reflections + p->max_transmissions > DCEM_MAX_REFLECTIONS)
     return fail(c, DCEM_E_INVALID_ARG, "max_reflections + max_transmissions must be <= %d", DCEM_MAX_REFLECTIONS);
   const int32_t slots = p->max_reflections + p->max_transmissions;   // interactions per path at most
-  const std::vector<uint32_t> bsets = branch_sets(slots, p->max_transmissions);
-  const int32_t n_branch = (int32_t)bsets.size();
-  const bool backward = p->trace_from_rx == 1;
-  const int32_t n_src = backward ? p->n_rx : p->n_tx, n_tgt = backward ? p->n_tx : p->n_rx;
-  const int64_t n_work = (int64_t)n_src * n_branch * p->n_rays;
+  int64_t n_branch = 1;   // as branch_sets has: the sets of at most max_transmissions of the slots
+  for (int64_t k = 1, of_size = 1; k <= p->max_transmissions; ++k) n_branch += of_size = of_size * (slots - k + 1) / k;
+  const int64_t n_work = (p->trace_from_rx ? p->n_rx : p->n_tx) * n_branch * p->n_rays;
   if (n_work >= (int64_t(1) << 31) - 1)
     return fail(c, DCEM_E_UNSUPPORTED, "work items per frame (sources x branches x n_rays) must be < 2^31 - 1");
   if ((int64_t)p->n_tx * p->n_rx >= (int64_t(1) << 27)) return fail(c, DCEM_E_UNSUPPORTED, "too many tx x rx pairs");
@@ -881,6 +876,27 @@ dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan
     if (bt + br + 4 + slots * (std::max(bf, 1) + (p->max_transmissions > 0 ? 1 : 0)) > 256)
       return fail(c, DCEM_E_UNSUPPORTED, "candidate key exceeds 256 bits");
   }
+  if (p->mem_kind == DCEM_MEM_HOST) {
+    auto finite = [](const float* v, size_t n) { return std::all_of(v, v + n, [](float x) { return std::isfinite(x); }); };
+    if (!finite(p->tx_pos, 3 * (size_t)p->n_tx)) return fail(c, DCEM_E_INVALID_ARG, "non-finite tx position");
+    if (!finite(p->rx_pos, 3 * (size_t)p->n_rx)) return fail(c, DCEM_E_INVALID_ARG, "non-finite rx position");
+    if (p->ray_dirs && !finite(p->ray_dirs, 3 * (size_t)p->n_rays))
+      return fail(c, DCEM_E_INVALID_ARG, "non-finite ray direction");
+  }
+  return DCEM_OK;
+}
+
+// Host part of a frame whose arguments were checked: the unread previous frame, the
+// configuration, uploads and buffers.  Enqueues nothing of the frame itself
+// beyond the uploads (and, when the rays changed, their directions and order).
+dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan) {
+  const bool visited = p->discovery == DCEM_DISCOVER_VISITED;
+  const int32_t slots = p->max_reflections + p->max_transmissions;
+  const std::vector<uint32_t> bsets = branch_sets(slots, p->max_transmissions);
+  const int32_t n_branch = (int32_t)bsets.size();
+  const bool backward = p->trace_from_rx == 1;
+  const int32_t n_src = backward ? p->n_rx : p->n_tx, n_tgt = backward ? p->n_tx : p->n_rx;
+  const int64_t n_work = (int64_t)n_src * n_branch * p->n_rays;
   HIP_TRY(hipSetDevice(c->device), "set device");
   // An unread previous frame is finished before anything of this frame
   // replaces its configuration or buffers: its results land in the frame
@@ -895,14 +911,13 @@ dcem_status frame_setup(dcem_ctx* c, const dcem_trace_params* p, FramePlan& plan
   std::vector<float> txh, rxh;
   HIP_TRY(fetch(txh, p->tx_pos, 3 * (size_t)p->n_tx, p->mem_kind, c->stream), "read tx");
   HIP_TRY(fetch(rxh, p->rx_pos, 3 * (size_t)p->n_rx, p->mem_kind, c->stream), "read rx");
-  for (float v : txh) if (!std::isfinite(v)) return fail(c, DCEM_E_INVALID_ARG, "non-finite tx position");
-  for (float v : rxh) if (!std::isfinite(v)) return fail(c, DCEM_E_INVALID_ARG, "non-finite rx position");
+  if (p->mem_kind == DCEM_MEM_DEVICE) {   // (host arrays: frame_check)
+    for (float v : txh) if (!std::isfinite(v)) return fail(c, DCEM_E_INVALID_ARG, "non-finite tx position");
+    for (float v : rxh) if (!std::isfinite(v)) return fail(c, DCEM_E_INVALID_ARG, "non-finite rx position");
+  }
   const bool fib = p->ray_dirs == nullptr;
   std::vector<float> dirh;
-  if (!fib && p->mem_kind == DCEM_MEM_HOST) {
-    dirh.assign(p->ray_dirs, p->ray_dirs + 3 * (size_t)p->n_rays);
-    for (float v : dirh) if (!std::isfinite(v)) return fail(c, DCEM_E_INVALID_ARG, "non-finite ray direction");
-  }
+  if (!fib && p->mem_kind == DCEM_MEM_HOST) dirh.assign(p->ray_dirs, p->ray_dirs + 3 * (size_t)p->n_rays);
   TraceConfig& cfg = c->cfg;
   // the trace's sources and targets (the receivers and transmitters when
   // tracing backward)
@@ -1132,7 +1147,8 @@ extern "C" {
 
 dcem_status dcem_trace_frame(dcem_ctx* c, const dcem_trace_params* p) {
   FramePlan plan;
-  dcem_status st = frame_setup(c, p, plan);
+  dcem_status st = frame_check(c, p);
+  if (st == DCEM_OK) st = frame_setup(c, p, plan);
   if (st == DCEM_OK) st = frame_front(c, plan);
   if (st == DCEM_OK) st = frame_trace(c, plan);
   if (st == DCEM_OK) st = frame_back(c, plan);
@@ -1611,6 +1627,10 @@ dcem_status spread_contexts(dcem_batch* b, const std::vector<FramePlan>& plan, P
 dcem_status batch_frame(dcem_batch* b, const dcem_trace_params* params, const dcem::BatchShape& shape, bool timed) {
   const int n = (int)b->ctx.size();
   std::vector<FramePlan> plan(n);
+  for (int j = 0; j < n; ++j) {   // all of them first: one context's bad arguments change none
+    const dcem_status st = frame_check(b->ctx[j], &params[j]);
+    if (st != DCEM_OK) return st;
+  }
   for (int j = 0; j < n; ++j) {
     const dcem_status st = frame_setup(b->ctx[j], &params[j], plan[j]);
     if (st != DCEM_OK) return st;

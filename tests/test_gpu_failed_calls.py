@@ -163,3 +163,32 @@ def test_refused_upload_keeps_the_scene():
         c.close()
     for a, b in zip(*got):
         assert np.array_equal(a, b, equal_nan=True)
+
+
+def test_refused_frames_keep_the_last():
+    """Bad arguments of one context of a batch, or of a frame, change no context."""
+    s = scenes.box_field(40, 3, half=60.0, n_rays=2000)
+    ctxs = [dcem.Context(0) for _ in range(3)]
+    batch = dcem.Batch(ctxs)
+    good = dcem.scene_frame_args(s, record_trace_log=True)
+    more = {**good, "max_reflections": 3, "n_rays": 9000, "freqs_hz": [28e9, 3e9]}
+    for c in ctxs:
+        c.scene_upload(s)
+    batch.trace([good] * 3)
+    want = outputs(ctxs[0])
+    far = np.asarray(s.rx, np.float32).copy()
+    far[3, 1] = np.inf
+    dirs = scenes.random_sphere_dirs(50, seed=1)
+    dirs[7, 2] = np.nan
+    for bad in ({"rx": far}, {"rx_radius": -1.0}, {"freqs_hz": [0.0]}, {"max_reflections": 11}, {"n_rays": -1},
+                {"ray_dirs": dirs, "n_rays": 50}, {"tx": np.float32([[0, 0, np.nan]])}):
+        for call in (lambda: batch.trace([more, more, {**good, **bad}]), lambda: ctxs[2].trace_frame(**{**good, **bad})):
+            with pytest.raises(dcem.DcemError) as e:
+                call()
+            assert e.value.status == dcem.E_INVALID_ARG, bad
+            for c in ctxs:
+                for a, b in zip(outputs(c), want):
+                    assert np.array_equal(a, b, equal_nan=True)
+    batch.close()
+    for c in ctxs:
+        c.close()
